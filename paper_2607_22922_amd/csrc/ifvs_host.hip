@@ -219,6 +219,7 @@ struct ifvs_index {
   int64_t stride64 = 0;
   unsigned long long* counts = nullptr;  // [max_batch]
   uint32_t* count_parts = nullptr;       // [max_batch][filter_count_parts(n)] per-workgroup pool sizes
+  FilterPlan* filter_plans = nullptr;    // [ceil(max_batch / kFilterGroup)][kFilterCols] value classes
   uint64_t* partials = nullptr;  // per-wavefront top-k keys
   size_t partial_keys = 0;
   // Gather scan of masked batches (null when M has no gather kernel).
@@ -327,6 +328,7 @@ struct ifvs_index {
                     static_cast<void*>(bound_parts),
                     static_cast<void*>(slot_order_dev),
                     static_cast<void*>(counts), static_cast<void*>(count_parts), static_cast<void*>(vstart),
+                    static_cast<void*>(filter_plans),
                     static_cast<void*>(partials), static_cast<void*>(codes_rm),
                     static_cast<void*>(lists), static_cast<void*>(list_n), static_cast<void*>(qmode),
                     static_cast<void*>(read_hist), static_cast<void*>(enc_params),
@@ -847,22 +849,69 @@ ifvs_status plan_scan(const ifvs_index* idx, int32_t nq, int32_t k, int32_t lut_
   return IFVS_OK;
 }
 
-ifvs_status filter_into_workspace(ifvs_index* idx, const SearchWs& ws, int32_t nq, bool residual_only,
-                                  bool counts, hipStream_t s) {
+// The columns that the batch's clauses (all effective ones, or the residual
+// ones) name and the bounds they put on them.
+FilterCols filter_columns(const ifvs_index* idx, const DevPred* host, int32_t nq, bool residual_only) {
+  FilterCols fc;
+  uint64_t top[kFilterCols] = {};          // largest bound + 1 of each column
+  int32_t count[kFilterCols] = {};
+  for (int32_t i = 0; i < nq; ++i) {
+    if (i % kFilterGroup == 0) std::fill(count, count + kFilterCols, 0);
+    const DevPred& p = host[i];
+    const int nc = p.n_eff < 0 ? 0 : (residual_only ? p.n_res : p.n_eff);
+    for (int j = 0; j < nc; ++j) {
+      const int32_t col = residual_only ? p.res_col[j] : p.col[j];
+      const uint32_t lo = static_cast<uint32_t>(residual_only ? p.res_lo[j] : p.lo[j]) ^ 0x80000000u;
+      const uint64_t hi = uint64_t{lo} + (residual_only ? p.res_width[j] : p.width[j]);
+      int c = 0;
+      while (c < fc.n && fc.col[c] != col) ++c;
+      if (c == kFilterCols) {
+        fc.n = kFilterCols + 1;
+        return fc;
+      }
+      if (c == fc.n) {
+        ++fc.n;
+        fc.col[c] = col;
+        fc.base[c] = lo;
+        top[c] = lo;
+      }
+      fc.base[c] = std::min(fc.base[c], lo);
+      top[c] = std::max<uint64_t>(top[c], hi < (uint64_t{1} << 32) ? hi : lo);
+      count[c] += 2;
+      fc.max_bounds[c] = std::max(fc.max_bounds[c], count[c]);
+    }
+  }
+  // No clause anywhere: one column with the single class of all its values.
+  if (fc.n == 0 && idx->n_attr > 0) fc.n = 1;
+  for (int c = 0; c < fc.n; ++c) {
+    if (fc.base[c] > 0) --fc.base[c];
+    const uint64_t entries = top[c] - fc.base[c] + 1;
+    fc.direct[c] = entries <= kFilterDirect ? static_cast<int32_t>(entries) : 0;
+  }
+  return fc;
+}
+
+// Selection words of the batch (`host`: its staged predicates) into the
+// workspace's bitmaps, or into `out` ([nq][stride] 32-bit words).
+ifvs_status filter_batch(ifvs_index* idx, const SearchWs& ws, const DevPred* host, int32_t nq, bool residual_only,
+                         bool id_order, bool counts, uint32_t* out, int64_t stride, hipStream_t s) {
+  const FilterCols fc = filter_columns(idx, host, nq, residual_only);
   IFVS_LAUNCH(idx, kStFilter, s, "launching filter kernel",
-              launch_filter(residual_only ? idx->attrs_phys : idx->attrs, idx->n, idx->n_attr,
-                            ws.preds, nq, residual_only, ws.bitmap, ws.stride64,
-                            counts ? ws.counts : nullptr, ws.count_parts, s));
+              launch_filter(id_order ? idx->attrs : idx->attrs_phys, idx->n, ws.preds, nq, residual_only, fc,
+                            idx->filter_plans, out, stride, counts ? ws.counts : nullptr, ws.count_parts, s));
   return IFVS_OK;
 }
 
-ifvs_status copy_bitmaps_out(ifvs_index* idx, const SearchWs& ws, int32_t nq, uint32_t* bitmap_out,
-                             hipStream_t s) {
-  const size_t words = static_cast<size_t>((idx->n + 31) / 32);
-  IFVS_HIP(hipMemcpy2DAsync(bitmap_out, words * 4, ws.bitmap, ws.stride64 * 8, words * 4, nq,
-                            hipMemcpyDeviceToDevice, s),
-           "copying bitmaps");
-  return IFVS_OK;
+ifvs_status filter_into_workspace(ifvs_index* idx, const SearchWs& ws, const DevPred* host, int32_t nq,
+                                  bool residual_only, bool counts, hipStream_t s) {
+  return filter_batch(idx, ws, host, nq, residual_only, false, counts, reinterpret_cast<uint32_t*>(ws.bitmap),
+                      2 * ws.stride64, s);
+}
+
+// The Filter stage's bitmaps in id order, straight into the caller's words.
+ifvs_status filter_into_output(ifvs_index* idx, const SearchWs& ws, const DevPred* host, int32_t nq, bool counts,
+                               uint32_t* bitmap_out, hipStream_t s) {
+  return filter_batch(idx, ws, host, nq, false, true, counts, bitmap_out, (idx->n + 31) / 32, s);
 }
 
 }  // namespace
@@ -1081,6 +1130,10 @@ ifvs_status ifvs_load_index(const ifvs_index_desc* desc, ifvs_index** out) {
   if ((st = dev_alloc(&idx->count_parts, static_cast<size_t>(d.max_batch) * filter_count_parts(idx->n),
                       "pool size partials")) != IFVS_OK)
     return bail(st);
+  if ((st = dev_alloc(&idx->filter_plans,
+                      static_cast<size_t>((d.max_batch + kFilterGroup - 1) / kFilterGroup) * kFilterCols,
+                      "filter value classes")) != IFVS_OK)
+    return bail(st);
   // Partials: room for at least 16 chunks per query, capped near 512 MB.
   {
     const size_t per_chunk = static_cast<size_t>(d.max_batch) * kScanWaves * d.max_k;
@@ -1214,10 +1267,10 @@ ifvs_status ifvs_filter(ifvs_index* idx, int32_t nq, const ifvs_predicate* preds
   hipStream_t s = static_cast<hipStream_t>(stream);
   IFVS_HIP(hipSetDevice(idx->device), "hipSetDevice");
   int slot = 0;
-  if (ifvs_status st = stage_predicates(idx, nq, preds, false, true, s, &slot); st != IFVS_OK) return st;
+  DevPred* host = nullptr;
+  if (ifvs_status st = stage_predicates(idx, nq, preds, false, true, s, &slot, &host); st != IFVS_OK) return st;
   const SearchWs ws = index_ws(idx);
-  if (ifvs_status st = filter_into_workspace(idx, ws, nq, false, true, s); st != IFVS_OK) return st;
-  if (ifvs_status st = copy_bitmaps_out(idx, ws, nq, bitmap_out, s); st != IFVS_OK) return st;
+  if (ifvs_status st = filter_into_output(idx, ws, host, nq, true, bitmap_out, s); st != IFVS_OK) return st;
   if (count_out)
     IFVS_HIP(hipMemcpyAsync(count_out, idx->counts, sizeof(int64_t) * nq, hipMemcpyDeviceToDevice, s),
              "copying pool sizes");
@@ -1481,10 +1534,8 @@ ifvs_status run_search(ifvs_index* idx, int32_t nq, const void* lut, int32_t lut
                 launch_topk_merge(ws.partials, nq, static_cast<int64_t>(list_jobs) * kScanWaves * k, k, ws.iv, 0,
                                   static_cast<int64_t>(kScanWaves) * k, ws.qorder, ids_out, dist_out, s,
                                   cl.n_keys));
-    if (bitmap_out) {
-      if (ifvs_status st = filter_into_workspace(idx, ws, nq, false, false, s); st != IFVS_OK) return st;
-      if (ifvs_status st = copy_bitmaps_out(idx, ws, nq, bitmap_out, s); st != IFVS_OK) return st;
-    }
+    if (bitmap_out)
+      if (ifvs_status st = filter_into_output(idx, ws, p.host, nq, false, bitmap_out, s); st != IFVS_OK) return st;
     ScanPlan lp{};
     lp.qtile = 1;
     lp.splits = list_splits;
@@ -1504,16 +1555,14 @@ ifvs_status run_search(ifvs_index* idx, int32_t nq, const void* lut, int32_t lut
                       static_cast<size_t>(idx->m) * kKsub * gather_lut + gather_lds_bytes(plan.pool_stride) <=
                           static_cast<size_t>(kLdsBudget);
   if (gather) {
-    IFVS_LAUNCH(idx, kStFilter, s, "launching filter kernel",
-                launch_filter(idx->attrs_phys, idx->n, idx->n_attr, ws.preds, nq, false, ws.bitmap,
-                              ws.stride64, ws.counts, ws.count_parts, s));
+    if (ifvs_status st = filter_into_workspace(idx, ws, p.host, nq, false, true, s); st != IFVS_OK) return st;
     const int64_t max_rows = idx->opt_gather == 1 ? ws.list_cap : std::min(ws.list_cap, gather_auto_rows(idx));
     IFVS_LAUNCH(idx, kStFilter, s, "launching compaction kernel",
                 launch_compact(ws.bitmap, ws.stride64, ws.counts, ws.count_parts,
                                filter_count_parts(idx->n), nq, max_rows, ws.list_cap, ws.lists,
                                ws.list_n, ws.qmode, s));
   } else if (need_bitmap) {
-    if (ifvs_status st = filter_into_workspace(idx, ws, nq, true, false, s); st != IFVS_OK) return st;
+    if (ifvs_status st = filter_into_workspace(idx, ws, p.host, nq, true, false, s); st != IFVS_OK) return st;
   }
   ScanBatch b{};
   b.codes_t = idx->codes_t;
@@ -1568,8 +1617,7 @@ ifvs_status run_search(ifvs_index* idx, int32_t nq, const void* lut, int32_t lut
   if (bitmap_out) {
     // The Filter stage's bitmaps in id order (the scan itself reads row
     // intervals and residual bits in the physical order).
-    if (ifvs_status st = filter_into_workspace(idx, ws, nq, false, false, s); st != IFVS_OK) return st;
-    if (ifvs_status st = copy_bitmaps_out(idx, ws, nq, bitmap_out, s); st != IFVS_OK) return st;
+    if (ifvs_status st = filter_into_output(idx, ws, p.host, nq, false, bitmap_out, s); st != IFVS_OK) return st;
   }
   idx->last_plan = plan;
   idx->last_coarse = false;
@@ -1884,7 +1932,7 @@ ifvs_status ifvs_exact_search(ifvs_index* idx, int32_t nq, const float* q, const
               launch_intervals(exact_intervals(idx, slot, nq), s));
   if (ifvs_status st = release_slot(idx, slot, s); st != IFVS_OK) return st;
   if (need_bitmap)
-    if (ifvs_status st = filter_into_workspace(idx, index_ws(idx), nq, true, false, s); st != IFVS_OK) return st;
+    if (ifvs_status st = filter_into_workspace(idx, index_ws(idx), host, nq, true, false, s); st != IFVS_OK) return st;
   IFVS_LAUNCH(idx, kStCondition, s, "launching exact query kernel",
               launch_exact_queries(q, idx->dim, nq, idx->qorder_dev, idx->xmax, idx->qb, idx->qn_x, idx->eps_x,
                                    idx->cand_n_x, s));

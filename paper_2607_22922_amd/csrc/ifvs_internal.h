@@ -15,7 +15,7 @@ constexpr int kLdsBudget = 160 * 1024;     // LDS bytes per workgroup on gfx950
 constexpr int kScanWaves = 8;              // wavefronts per scan workgroup
 constexpr int kScanPub = 2;                // best keys per (wavefront, query) published for the workgroup bound
 constexpr int kScanSeed = 8;               // seed candidates per wavefront (kScanWaves * kScanSeed = 64 >= k)
-constexpr int kFilterQueries = 16;         // predicates evaluated per attribute read
+constexpr int kFilterQueries = 16;         // predicates per workgroup of the per-pair tests
 constexpr int kReadHistEntries = 66;       // read-counting builds: tiles, reads by 1..64 lanes, tiles fetched whole
 constexpr int kLookupHistBytes = 272;      // LDS of the scan's read-counting build: 66 counters, padded
 constexpr int kCoarseMaxDim = 128;         // largest D with a coarse quantizer (a row held in registers)
@@ -117,8 +117,32 @@ hipError_t launch_relayout_codes(const uint8_t* codes, int64_t n, int m, int mw,
 // kFilterPartRows-row parts.
 constexpr int64_t kFilterPartRows = 4 * 64 * 64;
 int64_t filter_count_parts(int64_t n);
-hipError_t launch_filter(const int32_t* attrs, int64_t n, int n_attr, const DevPred* preds,
-                         int nq, bool residual_only, uint64_t* bitmap, int64_t stride64,
+// out: [nq][stride] 32-bit words, stride >= ceil(n / 32) and < ceil(n / 32) + 2.
+// The columns the batch's clauses name (filter_columns), and per (query
+// group, column) the value classes a plan kernel leaves for the main one.
+constexpr int kFilterCols = 4;             // most columns evaluated by value classes
+constexpr int kFilterGroup = 128;          // queries whose masks share a class
+constexpr int kFilterBounds = kFilterGroup * kMaxClauses * 2;
+constexpr int kFilterDirect = 8192;        // most entries of a value -> class table
+struct FilterCols {
+  int32_t n = 0;                           // columns named; > kFilterCols: no classes
+  int32_t col[kFilterCols] = {};
+  int32_t max_bounds[kFilterCols] = {};    // most bounds of any query group on the column
+  // The value table's first value (unsigned order) and entry count (0: the
+  // bounds are too wide apart): from just below the smallest bound to the
+  // largest, so other values have the class of its first or last entry.
+  uint32_t base[kFilterCols] = {};
+  int32_t direct[kFilterCols] = {};
+};
+struct FilterPlan {
+  int32_t n_bounds;
+  uint32_t bounds[kFilterBounds];
+  uint32_t masks[kFilterGroup / 32][kFilterBounds + 1];   // [32 queries][class]
+  uint16_t direct[kFilterDirect];
+};
+bool filter_has_classes(const FilterCols& fc);
+hipError_t launch_filter(const int32_t* attrs, int64_t n, const DevPred* preds, int nq, bool residual_only,
+                         const FilterCols& fc, FilterPlan* plans, uint32_t* out, int64_t stride,
                          unsigned long long* counts, uint32_t* count_parts, hipStream_t s);
 
 // rows_out (optional, [nq][h]): the hashed bank rows of each query.
