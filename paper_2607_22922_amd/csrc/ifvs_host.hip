@@ -67,6 +67,23 @@ constexpr int kStagingSlots = 8;
 // 1.26x at 10%).
 constexpr int64_t kCoarseAutoTiles = 8192;
 constexpr int kCoarseAutoM = 32;
+// Automatic screening: batches of 256 queries on 16-byte codes and 48-byte
+// codes took the tiled scan 8 and 11 ps, the screening 2.0 and 1.6 ps per
+// (64-row tile, query, subspace) and about 190 us for its small kernels, so it
+// pays from about 3e7 of them; twice that is asked for (a scan of M other than
+// 16, 48 or 120 takes at least three times as long).  Its sample (every 16th
+// block of tiles) has to hold rows about as near as the k-th nearest: with
+// fewer than kScreenRowsPerK selected rows for each of the k, its bound stays
+// loose and too many rows survive (100K rows, k = 100, M = 120: 1150 us, the
+// scan 700).
+constexpr int64_t kScreenAutoWork = 60'000'000;
+constexpr int64_t kScreenAutoWorkAnyM = 20'000'000;
+constexpr int64_t kScreenRowsPerK = 4096;
+constexpr int kScreenSample = 16;          // the bound's pass: every 16th block of tiles
+constexpr int kScreenSeedTiles = 128;      // sampled 64-row tiles per query
+// Packed units between a query's smallest possible distance and its bound:
+// an entry saturates at 63 of them.
+int screen_levels(int m) { return std::max(192, 8 * m); }
 // Radius quantiles that split each coarse list into its kBands bands.
 constexpr float kBandQuantiles[kBands - 1] = {0.5f, 0.85f, 0.97f};
 
@@ -229,6 +246,12 @@ struct ifvs_index {
   int32_t* list_n = nullptr;     // [max_batch]
   int32_t* qmode = nullptr;      // [max_batch] 1: gather scan
   int64_t list_cap = 0;
+  // Packed-table screening (null tab: no workspace).
+  uint32_t* scr_tab = nullptr;   // [ceil(scr_batch / kScreenGroup)][mw * 4][256]
+  int32_t* scr_lists = nullptr;  // [scr_batch][scr_cap] survivors
+  float* scr_f = nullptr;        // [scr_batch][mw * 4 + 2] smallest entries, bounds, scales
+  int32_t* scr_i = nullptr;      // [scr_batch][2] levels, survivor counts
+  int scr_batch = 0, scr_cap = 0;
 
   // Full-precision vectors (ifvs_load_vectors) and the exact search's
   // workspace.
@@ -273,6 +296,7 @@ struct ifvs_index {
   int opt_exact_plan = 0;      // ifvs_exact_search: 0 automatic, 1 direct, 2 screened
   int opt_shared_bound = 0;    // workgroup bound from the wavefronts' best distances: 0 auto, 1 off, 2 on
   int opt_seed_tiles = 0;      // seeded bound: 0 auto, 1 off, n > 1 at most n tiles per wavefront
+  int opt_screen = 0;   // packed-table screening: 0 automatic, 1 never, 2 whenever supported
   int opt_gather_auto_pct = 30;   // automatic mode: pools up to this % of the rows
   int profile_mask = 0;          // stages timed with HIP events (IFVS_OPT_PROFILE)
   // IFVS_OPT_COUNT_READS: scans run the read-counting build, which adds its
@@ -325,6 +349,8 @@ struct ifvs_index {
                     static_cast<void*>(perm), static_cast<void*>(bank), static_cast<void*>(W),
                     static_cast<void*>(preds_dev), static_cast<void*>(qorder_dev),
                     static_cast<void*>(iv_dev), static_cast<void*>(gthr_dev), static_cast<void*>(bitmap),
+                    static_cast<void*>(scr_tab), static_cast<void*>(scr_lists), static_cast<void*>(scr_f),
+                    static_cast<void*>(scr_i),
                     static_cast<void*>(bound_parts),
                     static_cast<void*>(slot_order_dev),
                     static_cast<void*>(counts), static_cast<void*>(count_parts), static_cast<void*>(vstart),
@@ -759,12 +785,15 @@ ifvs_status timed(ifvs_index* idx, int stage, hipStream_t s, const char* what, F
 // Largest pool (rows) the automatic mode scores from a row list.
 int64_t gather_auto_rows(const ifvs_index* idx) { return idx->n * idx->opt_gather_auto_pct / 100; }
 
+// fallback: the scan only serves queries the screening leaves (usually none):
+// equal chunks, few of them, so that the empty launch is short.
 // interval_batch: every query has a cluster-key interval; one query per tile
 // then keeps all lanes busy and the scan is bound by LDS lookups, so sharing
 // code tiles across queries would not help.  Otherwise (masked rows) tiles
 // of several queries share each pass over the codes.
 ifvs_status plan_scan(const ifvs_index* idx, int32_t nq, int32_t k, int32_t lut_dtype,
-                      bool interval_batch, int64_t span_tiles, size_t partial_keys, ScanPlan* plan) {
+                      bool interval_batch, int64_t span_tiles, size_t partial_keys, ScanPlan* plan,
+                      bool fallback = false) {
   const int lut_bytes = lut_dtype == IFVS_LUT_F16 ? 2 : 4;
   const int qmax = scan_max_qtile(idx->m, lut_bytes, k);
   if (qmax < 1)
@@ -795,7 +824,7 @@ ifvs_status plan_scan(const ifvs_index* idx, int32_t nq, int32_t k, int32_t lut_
     // into equal chunks, at least ~512 workgroups per batch.
     if (idx->opt_grid_tiles > 0) {
       plan->chunk_tiles = idx->opt_grid_tiles;
-    } else if (span_tiles >= 8192) {
+    } else if (span_tiles >= 8192 && !fallback) {
       const int64_t cells = (span_tiles + 5119) / 5120;
       plan->chunk_tiles = (span_tiles + cells - 1) / cells;
     }
@@ -1054,8 +1083,18 @@ ifvs_status ifvs_load_index(const ifvs_index_desc* desc, ifvs_index** out) {
       return bail(st);
     if ((st = dev_alloc(&idx->list_n, static_cast<size_t>(d.max_batch), "row list sizes")) != IFVS_OK)
       return bail(st);
-    if ((st = dev_alloc(&idx->qmode, static_cast<size_t>(d.max_batch), "scan modes")) != IFVS_OK)
-      return bail(st);
+  }
+  if ((st = dev_alloc(&idx->qmode, static_cast<size_t>(d.max_batch), "scan modes")) != IFVS_OK) return bail(st);
+  // Screening workspace: survivor lists of up to 32768 rows a query, 256 MiB
+  // for the batch.
+  if (screen_supported(d.m, 1)) {
+    idx->scr_batch = std::min(d.max_batch, kScreenBatch);
+    const size_t nb = static_cast<size_t>(idx->scr_batch), groups = (nb + kScreenGroup - 1) / kScreenGroup;
+    idx->scr_cap = static_cast<int>(std::min<int64_t>({32768, (int64_t{64} << 20) / idx->scr_batch, d.n}));
+    if ((st = dev_alloc(&idx->scr_tab, groups * idx->mw * 4 * kKsub, "packed tables")) != IFVS_OK) return bail(st);
+    if ((st = dev_alloc(&idx->scr_lists, nb * idx->scr_cap, "survivor lists")) != IFVS_OK) return bail(st);
+    if ((st = dev_alloc(&idx->scr_f, nb * (idx->mw * 4 + 2), "screening bounds")) != IFVS_OK) return bail(st);
+    if ((st = dev_alloc(&idx->scr_i, nb * 2, "survivor counts")) != IFVS_OK) return bail(st);
   }
   const size_t cb = static_cast<size_t>(d.m) * kKsub * idx->dsub;
   if ((st = dev_alloc(&idx->cpq, cb, "codebook")) != IFVS_OK) return bail(st);
@@ -1163,6 +1202,10 @@ ifvs_status ifvs_set_option(ifvs_index* idx, int32_t option, int64_t value) {
     case IFVS_OPT_GATHER:
       if (value > 2) return fail(IFVS_E_INVALID, "IFVS_OPT_GATHER takes 0, 1 or 2");
       idx->opt_gather = static_cast<int>(value);
+      return IFVS_OK;
+    case IFVS_OPT_SCREEN:
+      if (value > 2) return fail(IFVS_E_INVALID, "IFVS_OPT_SCREEN takes 0, 1 or 2");
+      idx->opt_screen = static_cast<int>(value);
       return IFVS_OK;
     case IFVS_OPT_SLOT_ORDER:
       if (value > 1) return fail(IFVS_E_INVALID, "IFVS_OPT_SLOT_ORDER takes 0 or 1");
@@ -1330,9 +1373,57 @@ struct SearchPrep {
   ScanPlan plan{};
   int list_jobs = 1;
   bool list_mode = false;
+  bool screen = false;          // packed-table screening first
+  int screen_chunk = 0, screen_splits = 0, screen_sample = 1, screen_seed = 0;
   bool ordered = false;
   int64_t n_order = 0;
 };
+
+// An option of the tiled scan is set.
+bool scan_options_set(const ifvs_index* idx) {
+  return idx->opt_qtile > 0 || idx->opt_splits > 0 || idx->opt_min_chunk > 0 || idx->opt_grid_tiles > 0 ||
+         idx->opt_grid_relative != 0 || idx->opt_slot_order != 0 || idx->opt_seed_tiles != 0 ||
+         idx->opt_shared_bound != 0;
+}
+
+// Whether a batch is screened, and its chunks.  The screening reads each code
+// tile of a group's hull once for its four queries where the scan reads each
+// query's tiles, and its other kernels take tens of microseconds.
+void plan_screen(const ifvs_index* idx, int32_t nq, int32_t k, const DevPred* host, const int32_t* qorder,
+                 const BatchShape& shape, SearchPrep& p) {
+  p.screen = false;
+  if (idx->opt_screen == 1 || !idx->scr_tab || nq > idx->scr_batch || !screen_supported(idx->m, k)) return;
+  int64_t sum_iv = 0, sum_hull = 0, max_hull = 1;
+  for (int g = 0; g < nq; g += kScreenGroup) {
+    int64_t lo = INT64_MAX, hi = 0;
+    for (int i = g; i < std::min(nq, g + kScreenGroup); ++i) {
+      const DevPred& d = host[qorder[i]];
+      int64_t a = 0, b = idx->n_tiles;
+      if (idx->n_cluster > 0) estimate_interval_range(idx, d, &a, &b);
+      if (d.n_eff < 0 || b <= a) continue;
+      sum_iv += b - a;
+      lo = std::min(lo, a);
+      hi = std::max(hi, b);
+    }
+    if (hi > lo) {
+      sum_hull += hi - lo;
+      max_hull = std::max(max_hull, hi - lo);
+    }
+  }
+  const bool fixed_m = idx->m == 16 || idx->m == 48 || idx->m == 120;
+  if (idx->opt_screen == 0 &&
+      (sum_iv * idx->m < (fixed_m ? kScreenAutoWork : kScreenAutoWorkAnyM) || sum_hull * 2 > sum_iv ||
+       sum_iv * kTileRows < kScreenRowsPerK * k * nq))
+    return;
+  p.screen = true;
+  // About 4096 workgroups, of 64 to 4096 tiles.
+  int64_t chunk = (sum_hull / 4096 + 63) / 64 * 64;
+  chunk = std::min<int64_t>(4096, std::max<int64_t>(64, chunk));
+  p.screen_chunk = static_cast<int>(chunk);
+  p.screen_splits = static_cast<int>(std::min<int64_t>(8192, max_hull / chunk + 2));
+  p.screen_seed = kScreenSeedTiles;
+  p.screen_sample = kScreenSample;
+}
 
 ifvs_status prepare_search(ifvs_index* idx, int32_t nq, const ifvs_predicate* preds, const void* lut,
                            int32_t lut_dtype, bool bounded, const float* alpha, int32_t k, int32_t* ids_out,
@@ -1392,6 +1483,14 @@ ifvs_status prepare_search(ifvs_index* idx, int32_t nq, const ifvs_predicate* pr
       list_scan_lds_bytes(idx->m, lut_dtype, pool_stride_for(k)) <= size_t{kLdsBudget} &&
       list_jobs_lds_bytes(nq) <= size_t{kLdsBudget} &&
       static_cast<size_t>(nq) * list_splits * kScanWaves * k <= ws.partial_keys;
+  // Screening, unless the scan itself was asked for (its own options).
+  if (!static_scratch && !p.list_mode && !idx->opt_count_reads && !scan_options_set(idx)) {
+    plan_screen(idx, nq, k, host, reinterpret_cast<const int32_t*>(host + idx->max_batch), shape, p);
+    if (p.screen)
+      if (ifvs_status st = plan_scan(idx, nq, k, lut_dtype, interval_batch, span, ws.partial_keys, &plan, true);
+          st != IFVS_OK)
+        return st;
+  }
   if (idx->opt_count_reads && !p.list_mode &&
       (!scan_can_count(idx->m, plan.qtile, lut_dtype) || plan.lds_bytes + kLookupHistBytes > size_t{kLdsBudget}))
     return fail(IFVS_E_UNSUPPORTED, "IFVS_OPT_COUNT_READS: no read-counting scan for this plan (it needs one query "
@@ -1564,6 +1663,43 @@ ifvs_status run_search(ifvs_index* idx, int32_t nq, const void* lut, int32_t lut
   } else if (need_bitmap) {
     if (ifvs_status st = filter_into_workspace(idx, ws, p.host, nq, true, false, s); st != IFVS_OK) return st;
   }
+  if (p.screen) {
+    ScreenBatch sb{};
+    sb.codes_t = idx->codes_t;
+    sb.m = idx->m;
+    sb.mw = idx->mw;
+    sb.lut = lut;
+    sb.nq = nq;
+    sb.qorder = ws.qorder;
+    sb.iv = ws.iv;
+    sb.preds = ws.preds;
+    sb.bitmap = ws.bitmap;
+    sb.stride64 = ws.stride64;
+    sb.perm = idx->perm;
+    sb.k = k;
+    sb.gathered = gather;
+    sb.mode = idx->qmode;
+    sb.gthr = ws.gthr;
+    sb.seed_tiles = p.screen_seed;
+    sb.levels = screen_levels(idx->m);
+    sb.chunk_tiles = p.screen_chunk;
+    sb.splits = p.screen_splits;
+    sb.sample = p.screen_sample;
+    sb.codes_rm = idx->codes_rm;
+    sb.rw = idx->rw;
+    sb.low = idx->scr_f;
+    sb.thr = idx->scr_f + static_cast<size_t>(idx->scr_batch) * idx->mw * 4;
+    sb.scale = sb.thr + idx->scr_batch;
+    sb.level = idx->scr_i;
+    sb.list_n = idx->scr_i + idx->scr_batch;
+    sb.lists = idx->scr_lists;
+    sb.list_cap = idx->scr_cap;
+    sb.tab = idx->scr_tab;
+    sb.ids_out = ids_out;
+    sb.dist_out = dist_out;
+    IFVS_LAUNCH(idx, kStScan, s, "launching screening kernels", launch_screen(sb, lut_dtype, s));
+  }
+  const int32_t* mode = gather ? ws.qmode : (p.screen ? idx->qmode : nullptr);
   ScanBatch b{};
   b.codes_t = idx->codes_t;
   b.n = idx->n;
@@ -1582,7 +1718,7 @@ ifvs_status run_search(ifvs_index* idx, int32_t nq, const void* lut, int32_t lut
   b.k = k;
   b.partials = ws.partials;
   b.gthr = ws.gthr;
-  b.mode = gather ? ws.qmode : nullptr;
+  b.mode = mode;
   b.slot_order = ordered ? ws.slot_order : nullptr;
   b.lookup_hist = idx->opt_count_reads ? idx->read_hist : nullptr;
   IFVS_LAUNCH(idx, kStScan, s, "launching scan kernel", launch_scan(b, plan, s));
@@ -1613,7 +1749,7 @@ ifvs_status run_search(ifvs_index* idx, int32_t nq, const void* lut, int32_t lut
   IFVS_LAUNCH(idx, kStMerge, s, "launching top-k merge kernel",
               launch_topk_merge(ws.partials, nq, per_query, k, ws.iv,
                                 plan.abs_cells ? plan.chunk_tiles : 0, static_cast<int64_t>(kScanWaves) * k,
-                                ws.qorder, ids_out, dist_out, s));
+                                ws.qorder, ids_out, dist_out, s, nullptr, mode));
   if (bitmap_out) {
     // The Filter stage's bitmaps in id order (the scan itself reads row
     // intervals and residual bits in the physical order).

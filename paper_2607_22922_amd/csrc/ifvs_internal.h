@@ -245,7 +245,7 @@ struct ScanBatch {
   int k;
   uint64_t* partials;           // [nq positions][splits][waves][k]
   uint64_t* gthr;               // [nq] shared thresholds, all-ones before the scan
-  const int32_t* mode;          // [nq] 1: the query is scored by the gather scan (null: none is)
+  const int32_t* mode;          // [nq] not 0: the query is scored elsewhere (1 gather scan, 2 screened; null: none)
   const int32_t* slot_order;    // chunk-grid dispatch order (null: slots in index order)
   unsigned long long* lookup_hist;  // [65] non-null: run the read-counting build (see scan_can_count)
 };
@@ -284,6 +284,51 @@ hipError_t launch_compact(const uint64_t* bitmap, int64_t stride64, const unsign
 hipError_t launch_gather_scan(const GatherBatch& b, hipStream_t s);
 
 hipError_t launch_scan(const ScanBatch& b, const ScanPlan& plan, hipStream_t s);
+
+// Packed-table screening (k_screen.hip): four queries per table read, the
+// survivors scored exactly, straight to the caller's outputs.
+constexpr int kScreenGroup = 4;            // queries whose entries share a table word
+constexpr int kScreenMaxK = 128;           // largest k (pools sorted in registers)
+constexpr int kScreenBatch = 4096;         // largest batch its workspace is sized for
+struct ScreenBatch {
+  const uint32_t* codes_t;
+  int m, mw;
+  const void* lut;              // [nq][m][256] by original query index
+  int nq;
+  const int32_t* qorder;        // position -> original query index
+  const int64_t* iv;
+  const DevPred* preds;
+  const uint64_t* bitmap;       // [nq][stride64] physical-order selection words
+  int64_t stride64;
+  const int32_t* perm;
+  int k;
+  bool gathered;                // mode holds 1 for queries the gather scan scores
+  int32_t* mode;                // [nq] out: 2 screened and answered, 0 left to the scan
+  uint64_t* gthr;               // [nq] the scan's shared thresholds (the seed lowers them)
+  int seed_tiles;               // tiles of a query's sample
+  int levels;                   // L: packed units between the smallest possible distance and T
+  int chunk_tiles, splits;      // tiles per workgroup (multiple of 64), workgroups per group
+  int sample;                   // > 1: tighten T over every sample-th block of tiles first
+  const uint32_t* codes_rm;     // [n][rw] row-major code words (null: none)
+  int rw;
+  // Workspace by position: smallest entry per subspace, T, units per distance,
+  // L (-1: not screened), the survivors; packed tables by group.
+  float* low;                   // [positions][mw * 4]
+  float* thr;
+  float* scale;
+  int32_t* level;
+  int32_t* list_n;
+  int32_t* lists;               // [positions][list_cap]
+  int list_cap;
+  uint32_t* tab;                // [groups][mw * 4][256]
+  int32_t* ids_out;
+  float* dist_out;
+  int step;                     // set by the launchers: every step-th block of tiles is screened
+  int kpl, pool_stride;
+  size_t rerank_table_bytes;
+};
+bool screen_supported(int m, int k);
+hipError_t launch_screen(ScreenBatch a, int lut_dtype, hipStream_t s);
 // Predicate encoder (k_encoder.hip): w_z [nq][D] of the predicates in
 // `preds` (device-readable DevPred records) through the packed parameters
 // (layout in ifvs.h), H <= 128 a multiple of 16, F <= 256 a multiple of 16.
@@ -431,7 +476,8 @@ hipError_t lds_gather_probe(int active, int iters, int wg_per_cu, int reps, hipS
 hipError_t launch_topk_merge(const uint64_t* partials, int nq, int64_t per_query, int k,
                              const int64_t* iv, int64_t cell_tiles, int64_t slot_keys,
                              const int32_t* qorder, int32_t* ids_out, float* dist_out,
-                             hipStream_t s, const int32_t* n_keys = nullptr);   // n_keys: keys per position
+                             hipStream_t s, const int32_t* n_keys = nullptr,    // n_keys: keys per position
+                             const int32_t* mode = nullptr);                    // mode[q] == 2: already written
 
 // Symmetric distance computation (k_sdc.hip): the codeword table
 // T[m][a][b] (at load) and a query's table, the rows T[m][enc(q)_m] laid

@@ -66,7 +66,7 @@ struct ScanArgs {
   int abs_cells;         // 1: chunk c is absolute grid cell c (all XCDs walk the same cells)
   uint64_t* partials;
   uint64_t* gthr;   // [nq] per original query: smallest k-th key any wavefront has published
-  const int32_t* mode;   // [nq] 1: scored by the gather scan instead (null: none)
+  const int32_t* mode;   // [nq] not 0: scored elsewhere (1 gather scan, 2 screened; null: none)
   // Dispatch order (null: index order): workgroup b scans item
   // slot_order[(b % kXcds) * per_xcd * splits + b / kXcds] of its XCD, item
   // c * per_xcd + t meaning chunk c of the XCD's t-th query tile.
@@ -177,6 +177,13 @@ void scan_kernel(const ScanArgs a) {
   int qid[QT];
 #pragma unroll
   for (int qi = 0; qi < QT; ++qi) qid[qi] = qi < qn ? a.qorder[q0 + qi] : 0;
+  if (a.mode) {
+    // Every query of the tile scored elsewhere: nothing to stage or write.
+    bool mine = false;
+#pragma unroll
+    for (int qi = 0; qi < QT; ++qi) mine = mine || (qi < qn && a.mode[qid[qi]] == 0);
+    if (!mine) return;
+  }
 
   // Their tables (global [q][m][c]).  With M fixed at compile time every
   // load of the staging is issued here, so the tables, the intervals below
@@ -212,7 +219,7 @@ void scan_kernel(const ScanArgs a) {
     if (qi < qn) {
       r0[qi] = a.iv[2 * qid[qi]];
       r1[qi] = a.iv[2 * qid[qi] + 1];
-      if (a.mode && a.mode[qid[qi]] == 1) r1[qi] = r0[qi];   // the gather scan scores it
+      if (a.mode && a.mode[qid[qi]] != 0) r1[qi] = r0[qi];   // scored elsewhere
       resid[qi] = a.preds[qid[qi]].residual_mask != 0;
       if (r1[qi] > r0[qi]) {
         hull_lo = min(hull_lo, r0[qi]);

@@ -25,12 +25,14 @@ __global__ __launch_bounds__(64) void topk_merge_kernel(const uint64_t* __restri
                                                         int64_t cell_tiles, int64_t slot_keys,
                                                         const int32_t* __restrict__ qorder,
                                                         const int32_t* __restrict__ n_keys,
+                                                        const int32_t* __restrict__ mode,
                                                         int32_t* __restrict__ ids_out,
                                                         float* __restrict__ dist_out) {
   extern __shared__ uint64_t pool[];
   const int pos = blockIdx.x;                 // position in the scan's query order
   const int q = qorder ? qorder[pos] : pos;   // original query index
   const int lane = threadIdx.x;
+  if (mode && mode[q] == 2) return;           // the screening wrote its answer
   int cnt = 0;
   uint64_t thr = kNoKey;
   const uint64_t* src = partials + static_cast<size_t>(pos) * per_query;
@@ -76,11 +78,11 @@ __global__ __launch_bounds__(64) void topk_merge_kernel(const uint64_t* __restri
 hipError_t launch_topk_merge(const uint64_t* partials, int nq, int64_t per_query, int k,
                              const int64_t* iv, int64_t cell_tiles, int64_t slot_keys,
                              const int32_t* qorder, int32_t* ids_out, float* dist_out,
-                             hipStream_t s, const int32_t* n_keys) {
+                             hipStream_t s, const int32_t* n_keys, const int32_t* mode) {
   const int kpl = pool_kpl(k);
   const size_t lds = static_cast<size_t>(64 * kpl) * sizeof(uint64_t);
   topk_merge_kernel<<<dim3(nq), dim3(64), lds, s>>>(partials, per_query, k, kpl, iv, cell_tiles,
-                                                    slot_keys, qorder, n_keys, ids_out, dist_out);
+                                                    slot_keys, qorder, n_keys, mode, ids_out, dist_out);
   return hipGetLastError();
 }
 

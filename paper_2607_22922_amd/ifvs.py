@@ -30,6 +30,7 @@ OPT_EXACT_PLAN = 10
 OPT_SEED_TILES = 11
 OPT_COUNT_READS = 12
 OPT_COARSE = 13
+OPT_SCREEN = 14
 STAGES = ("condition", "lut", "filter", "scan", "merge", "encode", "coarse")
 
 EXPORTED = ("ifvs_load_index", "ifvs_free_index", "ifvs_select_codebook", "ifvs_build_lut",

@@ -1,0 +1,126 @@
+"""Packed-table screening of shared rows: the same ids and distance bits as
+the tiled scan and the oracle.  Sizes at the edges of a 64-row tile, a
+wavefront's block of tiles and a workgroup's chunk; batches that are no whole
+group of four; subspace counts on both sides of the prefetched code words (6)
+and of a word's four; k at its limit and above the rows selected; tables with
+negative, NaN and infinite entries, and lists that overflow (equal rows), which
+keep the tiled scan."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from tests._gpu_util import check_search_row, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2607_22922_amd import ifvs
+    return ifvs
+
+
+def _np(t):
+    return t.detach().cpu().numpy()
+
+
+def _index(B, n, m, nq, k, cluster, seed, spread=256, domain=200):
+    rng = np.random.default_rng(seed)
+    codes = rng.integers(0, spread, size=(n, m), dtype=np.uint8)
+    attrs = np.stack([rng.integers(0, domain, n), rng.integers(0, 5, n)]).astype(np.int32)
+    idx = B.Index(torch.from_numpy(codes).cuda(), torch.zeros(m, 256, 1, device="cuda"),
+                  torch.from_numpy(attrs).cuda(), max_batch=nq, max_k=k, cluster_cols=cluster)
+    return idx, codes, attrs, rng
+
+
+def _preds(rng, nq, domain):
+    out = []
+    for i in range(nq):
+        lo = int(rng.integers(0, domain // 2))
+        out.append([(0, lo, lo + domain // 2)])
+        if i % 5 == 1:
+            out[-1].append((1, 0, 3))
+        if i % 11 == 7:
+            out[-1] = [(0, lo, lo + 1), (1, 2, 3)]       # few rows: at times fewer than k
+        if i % 13 == 12:
+            out[-1] = [(0, 5, 5)]                        # none
+    return out
+
+
+def _both(B, idx, preds, lut, k, dt):
+    out = []
+    for mode in (2, 1):
+        idx.set_option(B.OPT_SCREEN, mode)
+        ids, dist = idx.search(preds, lut, k, dt)
+        torch.cuda.synchronize()
+        out.append((_np(ids), _np(dist)))
+    idx.set_option(B.OPT_SCREEN, 0)
+    (ids, dist), (ids1, dist1) = out
+    assert np.array_equal(ids, ids1)
+    assert np.array_equal(dist.view(np.uint32), dist1.view(np.uint32))
+    return ids, dist
+
+
+def _check(lut, codes, attrs, preds, k, ids, dist, rows):
+    for i in rows:
+        cand = O.passing_ids(O.predicate_mask(attrs, preds[i]))
+        ids_o, dist_o = O.select_topk(O.adc_distances(_np(lut[i]).astype(np.float32), codes, cand), cand, k)
+        check_search_row(ids[i], dist[i], ids_o, dist_o, f"q{i} {preds[i]}")
+
+
+@pytest.mark.parametrize("n,m,nq,k,f16,cluster", [
+    (63, 3, 1, 1, False, ()), (65, 4, 5, 7, False, (0,)), (4095, 5, 4, 10, True, ()), (4097, 16, 9, 128, False, (0,)),
+    (33_001, 21, 6, 33, True, (0,)), (32_767, 24, 8, 10, False, ()), (40_000, 25, 7, 16, False, (1, 0)),
+    (70_001, 48, 13, 10, False, (0,)), (70_001, 48, 37, 100, True, ()), (50_003, 120, 11, 100, False, (0,)),
+    (300_007, 16, 40, 10, False, ()), (300_007, 8, 40, 100, False, (0, 1))])
+def test_screening_matches_scan_and_oracle(B, n, m, nq, k, f16, cluster):
+    say(f"[screen] n={n} m={m} nq={nq} k={k} f16={f16} cluster={cluster}")
+    idx, codes, attrs, rng = _index(B, n, m, nq, k, cluster, seed=n + m)
+    preds = _preds(rng, nq, 200)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    # a few near codewords, many far ones, as in a trained quantizer
+    lut = torch.rand(nq, m, 256, generator=g, device="cuda") ** 2 * 7 + 0.25 * torch.rand(nq, m, 1, generator=g, device="cuda")
+    dt = B.LUT_F16 if f16 else B.LUT_F32
+    lut = lut.half() if f16 else lut
+    ids, dist = _both(B, idx, preds, lut, k, dt)
+    _check(lut, codes, attrs, preds, k, ids, dist, range(min(nq, 13)))
+
+
+def test_screening_leaves_unbounded_queries_to_the_scan(B):
+    n, m, nq, k = 50_000, 12, 12, 10
+    say("[screen] negative, NaN, infinite, constant and tiny tables, equal rows")
+    idx, codes, attrs, rng = _index(B, n, m, nq, k, (), seed=5, spread=4)
+    preds = [[(0, 0, 150)]] * nq
+    lut = torch.rand(nq, m, 256, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    lut[1, 3, 2] = -0.5
+    lut[2, 0, 1] = float("nan")
+    lut[3, :, 1] = float("inf")
+    lut[4] = float("inf")
+    lut[5] = 0.25                      # every row at one distance: its list overflows
+    lut[6] = 0.0
+    lut[7] *= 1e-38
+    lut[8] *= 1e37
+    lut[9, 2:] = 0.0
+    ids, dist = _both(B, idx, preds, lut, k, B.LUT_F32)
+    _check(lut, codes, attrs, preds, k, ids, dist, [0, 1, 3, 5, 6, 7, 8, 9, 10, 11])
+
+
+def test_screening_is_chosen_by_work_and_sharing(B):
+    """A large batch over the same rows is screened automatically; every way
+    of asking for the tiled scan gives the same answer."""
+    n, m, nq, k = 400_000, 16, 256, 10
+    say("[screen] automatic")
+    idx, codes, attrs, rng = _index(B, n, m, nq, k, (), seed=9)
+    preds = _preds(rng, nq, 200)
+    lut = torch.rand(nq, m, 256, device="cuda", generator=torch.Generator(device="cuda").manual_seed(2)) ** 2
+    ids, dist = _both(B, idx, preds, lut, k, B.LUT_F32)
+    for opt, value in ((None, 0), (B.OPT_QTILE, 2), (B.OPT_GATHER, 2)):
+        if opt:
+            idx.set_option(opt, value)
+        i2, d2 = idx.search(preds, lut, k)
+        torch.cuda.synchronize()
+        if opt:
+            idx.set_option(opt, 0)
+        assert np.array_equal(_np(i2), ids) and np.array_equal(_np(d2).view(np.uint32), dist.view(np.uint32))
+    _check(lut, codes, attrs, preds, k, ids, dist, range(0, nq, 41))
