@@ -67,18 +67,32 @@ constexpr int kStagingSlots = 8;
 // 1.26x at 10%).
 constexpr int64_t kCoarseAutoTiles = 8192;
 constexpr int kCoarseAutoM = 32;
-// Automatic screening: batches of 256 queries on 16-byte codes and 48-byte
-// codes took the tiled scan 8 and 11 ps, the screening 2.0 and 1.6 ps per
-// (64-row tile, query, subspace) and about 190 us for its small kernels, so it
-// pays from about 3e7 of them; twice that is asked for (a scan of M other than
-// 16, 48 or 120 takes at least three times as long).  Its sample (every 16th
-// block of tiles) has to hold rows about as near as the k-th nearest: with
-// fewer than kScreenRowsPerK selected rows for each of the k, its bound stays
-// loose and too many rows survive (100K rows, k = 100, M = 120: 1150 us, the
-// scan 700).
-constexpr int64_t kScreenAutoWork = 60'000'000;
-constexpr int64_t kScreenAutoWorkAnyM = 20'000'000;
-constexpr int64_t kScreenRowsPerK = 4096;
+// Automatic screening, by W = (64-row tiles, query, subspace) triples of the
+// queries it would serve.  Measured (us, tiled scan -> screening): intervals of
+// M = 16 or 48, W = 8e6 155 -> 258, 1.9e7 339 -> 368 and 322 -> 254, 2.3e7 310
+// -> 311, 5.8e7 772 -> 466, 6.4e8 5110 -> 1640; masked, W = 4.8e7 1241 -> 445,
+// 7.7e8 8760 -> 1570 (clustered with clauses left to test row by row: 5e6 540
+// -> 197); other M, whose scan reads its tiles without looking ahead,
+// intervals of W = 4.7e5 278 -> 223, 4.7e6 688 -> 316, masked 4.8e5 287 -> 320,
+// 9.9e6 693 -> 351.  Intervals of M = 120 keep the scan: a group's packed
+// tables fill a CU's LDS and few tiles are left early (W = 1.1e8 915 -> 1189).
+constexpr int64_t kScreenAutoWork = 30'000'000;
+constexpr int64_t kScreenAutoWorkMasked = 5'000'000;
+constexpr int64_t kScreenAutoWorkAnyM = 400'000;
+constexpr int64_t kScreenAutoWorkAnyMasked = 2'000'000;
+// The sample (every 16th block of tiles) has to hold rows about as near as the
+// k-th nearest: with fewer selected rows than this for each of the k, the
+// bound stays loose and too many rows survive (M = 120, k = 100: 100K rows
+// 700 -> 1150 us; M = 48, k = 100: 400K rows 998 -> 613).
+constexpr int64_t kScreenRowsPerK = 2048;
+// Pools up to this share of a masked index stay with the gather scan, whose
+// time grows with the pool (4M x 48-byte codes, 256 queries: 2% 1294 us
+// against the screening's 2465, 5% 3336 against 2356; 10M, 3%: 4609 and 4820).
+// A masked batch is screened where that is less than the gather scan's 53 ps
+// a pooled row or the tiled scan's 11 ps a triple (M = 120, 6 queries of 200K
+// rows: gather 389 us, screening 490).
+constexpr int kScreenGatherPct = 3;
+constexpr int kAttrSample = 4096;          // sampled values per column (pool size estimates)
 constexpr int kScreenSample = 16;          // the bound's pass: every 16th block of tiles
 constexpr int kScreenSeedTiles = 128;      // sampled 64-row tiles per query
 // Packed units between a query's smallest possible distance and its bound:
@@ -287,6 +301,8 @@ struct ifvs_index {
   // the planner estimate each query's interval length without touching the
   // device.
   std::vector<int32_t> fence0, fence1;
+  // [n_attr] kAttrSample evenly spaced values of each column, sorted.
+  std::vector<std::vector<int32_t>> attr_sample;
 
   int opt_qtile = 0, opt_splits = 0, opt_min_chunk = 0;
   int64_t opt_grid_tiles = 0;
@@ -817,15 +833,22 @@ ifvs_status plan_scan(const ifvs_index* idx, int32_t nq, int32_t k, int32_t lut_
   plan->abs_cells = false;
   plan->seed_tiles = 0;
   if (interval_batch) {
+    // A few queries over long spans leave most CUs without a cell of the grid
+    // below, so they are cut into equal chunks, as many as the merge's one
+    // wavefront per query reads in passing (512 keys a wavefront of the scan):
+    // three queries over 12K tiles of M = 120, k = 1 (9 cells) 807 -> 272 us;
+    // forty over 24K tiles of M = 16 keep the grid (507 us, 661 in 13 equal
+    // chunks), and so do two over 151K with k = 73 (724, 962).
     // Long spans (>= 8192 tiles) are cut on a chunk grid of cells of about
     // 5K tiles (measured best between 4K and 5K on 10M x 48-byte codes), so
     // queries with nearby spans read the same cells at the same time; a span
     // not aligned to the grid touches one cell more.  Short spans are cut
     // into equal chunks, at least ~512 workgroups per batch.
+    const int64_t many_splits = std::max(16, std::min(64, 512 / k));
     if (idx->opt_grid_tiles > 0) {
       plan->chunk_tiles = idx->opt_grid_tiles;
-    } else if (span_tiles >= 8192 && !fallback) {
-      const int64_t cells = (span_tiles + 5119) / 5120;
+    } else if (const int64_t cells = (span_tiles + 5119) / 5120;
+               span_tiles >= 8192 && !fallback && (gy * cells > 16 || many_splits < 2 * cells)) {
       plan->chunk_tiles = (span_tiles + cells - 1) / cells;
     }
     // Seeded bound (one query per tile, tables of a fixed M).  Automatic on
@@ -851,7 +874,8 @@ ifvs_status plan_scan(const ifvs_index* idx, int32_t nq, int32_t k, int32_t lut_
     else if (plan->chunk_tiles > 0)
       splits = (span_tiles + plan->chunk_tiles - 1) / plan->chunk_tiles + 1;
     else
-      splits = std::min<int64_t>(16, std::max<int64_t>((span_tiles + 8191) / 8192, (512 + gy - 1) / gy));
+      splits = std::min<int64_t>(span_tiles >= 8192 && !fallback ? many_splits : 16,
+                                 std::max<int64_t>((span_tiles + 8191) / 8192, (512 + gy - 1) / gy));
   }
   if (idx->opt_splits > 0) splits = idx->opt_splits;
   splits = std::min<int64_t>(splits, std::max<int64_t>(1, (idx->n_tiles + plan->min_chunk - 1) / plan->min_chunk));
@@ -888,6 +912,7 @@ FilterCols filter_columns(const ifvs_index* idx, const DevPred* host, int32_t nq
     if (i % kFilterGroup == 0) std::fill(count, count + kFilterCols, 0);
     const DevPred& p = host[i];
     const int nc = p.n_eff < 0 ? 0 : (residual_only ? p.n_res : p.n_eff);
+    fc.one_clause = fc.one_clause && nc <= 1;
     for (int j = 0; j < nc; ++j) {
       const int32_t col = residual_only ? p.res_col[j] : p.col[j];
       const uint32_t lo = static_cast<uint32_t>(residual_only ? p.res_lo[j] : p.lo[j]) ^ 0x80000000u;
@@ -1009,6 +1034,21 @@ ifvs_status ifvs_load_index(const ifvs_index_desc* desc, ifvs_index** out) {
       return bail(hip_fail(e, "loading attributes"));
   }
   idx->attrs_phys = idx->attrs;
+  if (d.n_attr > 0) {
+    const int per = static_cast<int>(std::min<int64_t>(d.n, kAttrSample));
+    int32_t* dev = nullptr;
+    if ((st = dev_alloc(&dev, static_cast<size_t>(d.n_attr) * per, "attribute samples")) != IFVS_OK) return bail(st);
+    std::vector<int32_t> host(static_cast<size_t>(d.n_attr) * per);
+    hipError_t e = launch_sample_attrs(idx->attrs, d.n, d.n_attr, per, dev, nullptr);
+    if (e == hipSuccess) e = hipMemcpy(host.data(), dev, host.size() * sizeof(int32_t), hipMemcpyDeviceToHost);
+    hipFree(dev);
+    if (e != hipSuccess) return bail(hip_fail(e, "sampling attributes"));
+    for (int c = 0; c < d.n_attr; ++c) {
+      idx->attr_sample.emplace_back(host.begin() + static_cast<int64_t>(c) * per,
+                                    host.begin() + static_cast<int64_t>(c + 1) * per);
+      std::sort(idx->attr_sample.back().begin(), idx->attr_sample.back().end());
+    }
+  }
   if (d.n_cluster > 0) {
     if ((st = dev_alloc(&idx->perm, static_cast<size_t>(d.n), "cluster permutation")) != IFVS_OK) return bail(st);
     if (hipError_t e = cluster_permutation(idx->attrs, d.n, d.n_cluster, idx->c0, idx->c1, idx->perm, nullptr);
@@ -1386,6 +1426,19 @@ bool scan_options_set(const ifvs_index* idx) {
          idx->opt_shared_bound != 0;
 }
 
+// Share of the rows that a predicate's clauses pass, from the columns' sampled
+// values (taken as independent).
+double estimate_share(const ifvs_index* idx, const DevPred& d) {
+  double share = d.n_eff < 0 ? 0.0 : 1.0;
+  for (int j = 0; j < d.n_eff; ++j) {
+    const auto& v = idx->attr_sample[d.col[j]];
+    const int64_t lo = d.lo[j], hi = lo + static_cast<int64_t>(d.width[j]);
+    const auto in = std::lower_bound(v.begin(), v.end(), hi) - std::lower_bound(v.begin(), v.end(), lo);
+    share *= static_cast<double>(in) / static_cast<double>(v.size());
+  }
+  return share;
+}
+
 // Whether a batch is screened, and its chunks.  The screening reads each code
 // tile of a group's hull once for its four queries where the scan reads each
 // query's tiles, and its other kernels take tens of microseconds.
@@ -1393,14 +1446,35 @@ void plan_screen(const ifvs_index* idx, int32_t nq, int32_t k, const DevPred* ho
                  const BatchShape& shape, SearchPrep& p) {
   p.screen = false;
   if (idx->opt_screen == 1 || !idx->scr_tab || nq > idx->scr_batch || !screen_supported(idx->m, k)) return;
-  int64_t sum_iv = 0, sum_hull = 0, max_hull = 1;
-  for (int g = 0; g < nq; g += kScreenGroup) {
+  const bool fixed_m = idx->m == 16 || idx->m == 48 || idx->m == 120;
+  const bool masked = !shape.interval_batch;
+  const int64_t least = fixed_m ? (masked || shape.need_bitmap ? kScreenAutoWorkMasked : kScreenAutoWork)
+                                : (masked ? kScreenAutoWorkAnyMasked : kScreenAutoWorkAnyM);
+  const bool automatic = idx->opt_screen == 0;
+  const int64_t widest = shape.interval_batch ? shape.span : idx->n_tiles;
+  if (automatic && (static_cast<int64_t>(nq) * widest * idx->m < least || (shape.interval_batch && idx->m == 120)))
+    return;
+  int64_t sum_iv = 0, sum_hull = 0, max_hull = 1, served = 0;
+  const bool gather_able = automatic && masked && idx->codes_rm && idx->opt_gather != 2;
+  double otherwise_us = 0.0;   // masked: what the served queries would take in the gather or the tiled scan
+  // At most 16 groups are looked at, evenly spaced (the sums scaled up): the
+  // planning of a batch stays within a few microseconds.
+  const int groups = (nq + kScreenGroup - 1) / kScreenGroup, looked = std::min(groups, 16);
+  for (int i0 = 0; i0 < looked; ++i0) {
+    const int g = i0 * groups / looked * kScreenGroup;
     int64_t lo = INT64_MAX, hi = 0;
     for (int i = g; i < std::min(nq, g + kScreenGroup); ++i) {
       const DevPred& d = host[qorder[i]];
       int64_t a = 0, b = idx->n_tiles;
       if (idx->n_cluster > 0) estimate_interval_range(idx, d, &a, &b);
       if (d.n_eff < 0 || b <= a) continue;
+      if (gather_able) {
+        const double share = estimate_share(idx, d);
+        if (share * 100.0 <= kScreenGatherPct) continue;
+        otherwise_us += share * 100.0 <= idx->opt_gather_auto_pct ? 53e-6 * share * static_cast<double>(idx->n)
+                                                                  : 11e-6 * static_cast<double>(b - a) * idx->m;
+      }
+      ++served;
       sum_iv += b - a;
       lo = std::min(lo, a);
       hi = std::max(hi, b);
@@ -1410,14 +1484,16 @@ void plan_screen(const ifvs_index* idx, int32_t nq, int32_t k, const DevPred* ho
       max_hull = std::max(max_hull, hi - lo);
     }
   }
-  const bool fixed_m = idx->m == 16 || idx->m == 48 || idx->m == 120;
-  if (idx->opt_screen == 0 &&
-      (sum_iv * idx->m < (fixed_m ? kScreenAutoWork : kScreenAutoWorkAnyM) || sum_hull * 2 > sum_iv ||
-       sum_iv * kTileRows < kScreenRowsPerK * k * nq))
-    return;
+  const int64_t total_iv = sum_iv * groups / looked, total_hull = sum_hull * groups / looked;
+  if (automatic) {
+    if (served == 0 || total_iv * idx->m < least || sum_hull * (fixed_m ? 2 : 1) > sum_iv ||
+        (fixed_m && sum_iv * kTileRows < kScreenRowsPerK * k * served))
+      return;
+    if (gather_able && otherwise_us * groups / looked < 250.0 + 1.7e-6 * static_cast<double>(total_iv * idx->m)) return;
+  }
   p.screen = true;
   // About 4096 workgroups, of 64 to 4096 tiles.
-  int64_t chunk = (sum_hull / 4096 + 63) / 64 * 64;
+  int64_t chunk = (total_hull / 4096 + 63) / 64 * 64;
   chunk = std::min<int64_t>(4096, std::max<int64_t>(64, chunk));
   p.screen_chunk = static_cast<int>(chunk);
   p.screen_splits = static_cast<int>(std::min<int64_t>(8192, max_hull / chunk + 2));
@@ -1655,7 +1731,9 @@ ifvs_status run_search(ifvs_index* idx, int32_t nq, const void* lut, int32_t lut
                           static_cast<size_t>(kLdsBudget);
   if (gather) {
     if (ifvs_status st = filter_into_workspace(idx, ws, p.host, nq, false, true, s); st != IFVS_OK) return st;
-    const int64_t max_rows = idx->opt_gather == 1 ? ws.list_cap : std::min(ws.list_cap, gather_auto_rows(idx));
+    const int64_t auto_rows =
+        p.screen && idx->opt_screen == 0 ? idx->n * kScreenGatherPct / 100 : gather_auto_rows(idx);
+    const int64_t max_rows = idx->opt_gather == 1 ? ws.list_cap : std::min(ws.list_cap, auto_rows);
     IFVS_LAUNCH(idx, kStFilter, s, "launching compaction kernel",
                 launch_compact(ws.bitmap, ws.stride64, ws.counts, ws.count_parts,
                                filter_count_parts(idx->n), nq, max_rows, ws.list_cap, ws.lists,

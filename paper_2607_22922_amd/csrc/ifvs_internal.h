@@ -76,6 +76,8 @@ hipError_t cluster_permutation(const int32_t* attrs, int64_t n, int n_cluster, i
                                int32_t* perm, hipStream_t s);
 hipError_t launch_gather_attrs(const int32_t* attrs, int64_t n, int n_attr, const int32_t* perm,
                                int32_t* attrs_phys, hipStream_t s);
+// out[c][i] = attrs[c][i * n / per]: evenly spaced values of every column.
+hipError_t launch_sample_attrs(const int32_t* attrs, int64_t n, int n_attr, int per, int32_t* out, hipStream_t s);
 // Row interval [iv[2q], iv[2q+1]) of every query on the clustered layout
 // (whole index for predicates without a cluster-key interval).  Reads the
 // predicates and the scan order from the staging slot (pinned host memory)
@@ -126,6 +128,7 @@ constexpr int kFilterBounds = kFilterGroup * kMaxClauses * 2;
 constexpr int kFilterDirect = 8192;        // most entries of a value -> class table
 struct FilterCols {
   int32_t n = 0;                           // columns named; > kFilterCols: no classes
+  bool one_clause = true;                  // no predicate has more than one clause
   int32_t col[kFilterCols] = {};
   int32_t max_bounds[kFilterCols] = {};    // most bounds of any query group on the column
   // The value table's first value (unsigned order) and entry count (0: the

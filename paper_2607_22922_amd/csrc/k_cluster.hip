@@ -40,6 +40,12 @@ __global__ void gather_attrs_kernel(const int32_t* __restrict__ attrs, int64_t n
   }
 }
 
+__global__ void sample_attrs_kernel(const int32_t* __restrict__ attrs, int64_t n, int n_attr, int per,
+                                    int32_t* __restrict__ out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n_attr * per) out[i] = attrs[static_cast<int64_t>(i / per) * n + static_cast<int64_t>(i % per) * n / per];
+}
+
 // Two wavefronts per query (lower and upper bound), one per workgroup; the
 // dispatch-order copy is spread over all of them.
 __global__ __launch_bounds__(64) void intervals_kernel(const IntervalArgs a) {
@@ -87,6 +93,11 @@ hipError_t cluster_permutation(const int32_t* attrs, int64_t n, int n_cluster, i
 hipError_t launch_gather_attrs(const int32_t* attrs, int64_t n, int n_attr, const int32_t* perm,
                                int32_t* attrs_phys, hipStream_t s) {
   gather_attrs_kernel<<<grid_for(n * n_attr), 256, 0, s>>>(attrs, n, n_attr, perm, attrs_phys);
+  return hipGetLastError();
+}
+
+hipError_t launch_sample_attrs(const int32_t* attrs, int64_t n, int n_attr, int per, int32_t* out, hipStream_t s) {
+  sample_attrs_kernel<<<grid_for(static_cast<int64_t>(n_attr) * per), 256, 0, s>>>(attrs, n, n_attr, per, out);
   return hipGetLastError();
 }
 

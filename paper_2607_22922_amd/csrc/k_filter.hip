@@ -553,11 +553,16 @@ hipError_t launch_filter_class(const int32_t* attrs, int64_t n, const FilterCols
 // the row count.  Measured against the per-pair tests (whole calls): 10K rows,
 // one query 25.2 us against 26.5; 100K rows, 60 queries 29.5 against 30.3; 1M
 // rows, 60 queries 30.6 against 37.5; 10M rows, 60 queries 72 against 177.
+// One clause a query, few pairs: the per-pair tests of one column are one
+// launch without a plan (390K rows, 127 queries 18.4 us against 15 + 14; 16K
+// rows, 60 queries 20.6 against 7 + 26; 1M rows, 60 queries slower, above).
 // (One group's clauses have at most kFilterBounds bounds in all, which fit
 // the LDS; groups that put that many on different columns may not.)
 bool filter_has_classes(const FilterCols& fc) {
   return fc.n >= 1 && fc.n <= kFilterCols && filter_class_lds(fc) + kFilterGroup * sizeof(uint32_t) <= kLdsBudget;
 }
+
+constexpr int64_t kPairTests = 50'000'000;   // (row, query) pairs
 
 hipError_t launch_filter(const int32_t* attrs, int64_t n, const DevPred* preds, int nq, bool residual_only,
                          const FilterCols& fc, FilterPlan* plans, uint32_t* out, int64_t stride,
@@ -565,7 +570,8 @@ hipError_t launch_filter(const int32_t* attrs, int64_t n, const DevPred* preds, 
   const unsigned parts = static_cast<unsigned>(filter_count_parts(n));
   uint32_t* cp = counts ? count_parts : nullptr;
   hipError_t e = hipSuccess;
-  if (filter_has_classes(fc)) {
+  const bool few = fc.n == 1 && fc.one_clause && n * nq <= kPairTests;
+  if (!few && filter_has_classes(fc)) {
     const unsigned groups = static_cast<unsigned>((nq + kFilterGroup - 1) / kFilterGroup);
     filter_plan_kernel<<<dim3(static_cast<unsigned>(fc.n), groups), dim3(kPlanThreads), 0, s>>>(
         preds, nq, residual_only ? 1 : 0, fc, plans);
