@@ -2183,7 +2183,14 @@ ifvs_status ifvs_exact_search(ifvs_index* idx, int32_t nq, const float* q, const
     int bin_lanes = 32;
     while (bin_lanes > 1 && short_rows / (lane_rows * bin_lanes) < 4 * static_cast<int64_t>(k)) bin_lanes /= 2;
     while (exact_bins_per_query(static_cast<int>(splits), bin_lanes) > idx->bins_cap) bin_lanes *= 2;
+    // Pass 1's sample: its bound is the (step k)-th smallest instead of the
+    // k-th, so step k is kept well below the candidate lists; at least four
+    // tiles a wavefront, and bins enough over the shortest interval.
+    int64_t step = 1;
+    if (short_rows / lane_rows >= 4 * static_cast<int64_t>(k))
+      step = std::max<int64_t>(1, std::min<int64_t>({8, lane_rows / 4, 1024 / k}));
     ExactScreen e{};
+    e.step = static_cast<int>(step);
     e.bin_lanes = bin_lanes;
     e.xb = idx->xb;
     e.xn = idx->xn;

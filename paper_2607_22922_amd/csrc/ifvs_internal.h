@@ -523,6 +523,7 @@ struct ExactScreen {
   int nq;
   int64_t chunk_rows;
   int splits;
+  int step;               // pass 1 reads a wavefront's every step-th tile
   int bin_lanes;          // lanes (power of two <= 32) whose row minima share a bin
   float* bins;            // [positions][exact_bins_per_query(splits, bin_lanes)]
   int32_t* cand;          // [positions][cand_cap]
