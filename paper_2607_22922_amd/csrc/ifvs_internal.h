@@ -170,6 +170,7 @@ struct TrainArgs {
   const int32_t* cand;       // [nq][n_cand] original ids (-1: absent), the first n_pos positives
   int nq, n_cand, n_pos;
   float tau, lam;
+  int code_lds;              // set by the launcher: the candidates' code words are staged in LDS
   float* loss;               // [nq]
   float* gdelta;             // [nq][m][256][dsub]
   float* galpha;             // [nq][m*r]

@@ -13,14 +13,23 @@
 //   3. the table gradient g_lut[m][c] = sum over candidates v whose code in
 //      subspace m is c of g_v, the candidates added in order by one
 //      wavefront (lane = subspace), in the table's LDS;
-//   4. one thread per codeword c: for every subspace and sub-dimension j,
+//   4. one thread per codeword c (four groups of 256 threads, each a quarter
+//      of the subspaces): for every subspace and sub-dimension j,
 //      Delta, e = q - C_PQ - Delta, the Delta gradient
 //        gd = g_lut * (-2 w e) + (2 lam / (M K d) / nq) Delta
 //      (stored for the W update), and the reductions over c of gd * W
 //      (alpha gradient) and g_lut * e^2 (w_f gradient): a wavefront
 //      reduction each, the four wavefronts' partials added in wave order.
-// train_update_w: W -= lr * sum_q gd_q (x) alpha_q, one thread per entry, the
-// queries summed in order.
+// The kernel is bound by latency: one workgroup per CU, so the candidates'
+// code words are fetched side by side into LDS (a serial chain of loads per
+// candidate before), sixteen wavefronts share the subspaces instead of four,
+// and a subspace's W and Delta-gradient values stay in registers between their
+// two uses (d of 2, 4 or 8 with r = 8).  256 queries, M = 48, d = 2, 42
+// candidates: 340 -> 72 us.
+// train_update_w: W -= lr * sum_q gd_q (x) alpha_q: a thread holds the r sums
+// of one (subspace, codeword, sub-dimension), so a gradient is read once and
+// not r times, over a quarter of the queries in order; the quarters are added
+// in order (69 -> 33 us at that shape).
 // train_update_bank: bank[row] -= lr * (sum of g_alpha over the (query, hash
 // function) pairs that hit the row, in pair order; a row hit twice gets
 // both), applied by the row's first pair.
@@ -34,7 +43,9 @@ namespace ifvs {
 
 namespace {
 
-constexpr int kTrainThreads = 256;
+constexpr int kTrainThreads = 1024;
+constexpr int kTrainWaves = kTrainThreads / 64;
+constexpr int kTrainGroups = kTrainThreads / kKsub;
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
@@ -66,28 +77,44 @@ __device__ __forceinline__ int code_of(const TrainArgs& a, int64_t row, int mm) 
   return static_cast<int>((w >> (8 * (mm & 3))) & 0xFFu);
 }
 
+// D, R: the fixed sub-dimension and direction counts (0: any).
+template <int D, int R>
 __global__ __launch_bounds__(kTrainThreads) void train_query_kernel(const TrainArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int qi = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int M = a.m, d = a.dsub, r = a.r, mr = a.m * a.r;
+  const int M = a.m, d = D > 0 ? D : a.dsub, r = R > 0 ? R : a.r, mr = a.m * r;
   float* s_tab = reinterpret_cast<float*>(smem);                 // [M][256]: table, then its gradient
   float* s_v = s_tab + M * kKsub;                                 // [n_cand]: distances, then g_v
   float* s_gw = s_v + a.n_cand;                                   // [4][dim]: w_f gradient, per wavefront
   float* s_ga = s_gw + 4 * a.dim;                                 // [4][M*r]: alpha gradient, per wavefront
-  double* s_red = reinterpret_cast<double*>(s_ga + 4 * mr + ((4 * mr + 4 * a.dim + a.n_cand) & 1));   // [3][4]
+  // Reductions ([3][kTrainWaves]) use the table's LDS while it holds nothing:
+  // after the distances, and after the gradients.
+  double* s_red = reinterpret_cast<double*>(smem);
+  static_assert(3 * kTrainWaves * sizeof(double) <= kKsub * sizeof(float), "one subspace's table holds them");
+  uint32_t* s_code = reinterpret_cast<uint32_t*>(s_ga + 4 * mr);   // [n_cand][mw] code words (code_lds)
 
   const float* lut = a.lut + static_cast<int64_t>(qi) * M * kKsub;
   for (int e = tid; e < M * kKsub; e += kTrainThreads) s_tab[e] = lut[e];
+  if (a.code_lds)
+    for (int e = tid; e < a.n_cand * a.mw; e += kTrainThreads) {
+      const int64_t id = cand_id(a, qi, e / a.mw);
+      const int64_t row = id < 0 ? 0 : (a.inv_perm ? a.inv_perm[id] : id);
+      s_code[e] = a.codes_t[((row >> 6) * a.mw + e % a.mw) * 64 + (row & 63)];
+    }
   __syncthreads();
+  auto code_at = [&](int v, int64_t row, int mm) -> int {
+    if (a.code_lds) return static_cast<int>((s_code[v * a.mw + (mm >> 2)] >> (8 * (mm & 3))) & 0xFFu);
+    return code_of(a, row, mm);
+  };
 
   // 1. Distances.
   for (int v = tid; v < a.n_cand; v += kTrainThreads) {
     const int64_t id = cand_id(a, qi, v);
     float dist = 0.0f;
     if (id >= 0) {
-      const int64_t row = a.inv_perm ? a.inv_perm[id] : id;
-      for (int mm = 0; mm < M; ++mm) dist = __fadd_rn(dist, s_tab[mm * kKsub + code_of(a, row, mm)]);
+      const int64_t row = a.code_lds ? 0 : (a.inv_perm ? a.inv_perm[id] : id);
+      for (int mm = 0; mm < M; ++mm) dist = __fadd_rn(dist, s_tab[mm * kKsub + code_at(v, row, mm)]);
     }
     s_v[v] = dist;
   }
@@ -109,13 +136,18 @@ __global__ __launch_bounds__(kTrainThreads) void train_query_kernel(const TrainA
   n_p = wave_sum_d(n_p);
   if (lane == 0) {
     s_red[wave] = mx;
-    s_red[4 + wave] = pos_sum;
-    s_red[8 + wave] = n_p;
+    s_red[kTrainWaves + wave] = pos_sum;
+    s_red[2 * kTrainWaves + wave] = n_p;
   }
   __syncthreads();
-  mx = fmax(fmax(s_red[0], s_red[1]), fmax(s_red[2], s_red[3]));
-  pos_sum = s_red[4] + s_red[5] + s_red[6] + s_red[7];
-  n_p = s_red[8] + s_red[9] + s_red[10] + s_red[11];
+  mx = s_red[0];
+  pos_sum = n_p = 0.0;
+#pragma unroll
+  for (int w = 0; w < kTrainWaves; ++w) {
+    mx = fmax(mx, s_red[w]);
+    pos_sum += s_red[kTrainWaves + w];
+    n_p += s_red[2 * kTrainWaves + w];
+  }
   __syncthreads();
   double z = 0.0;
   for (int v = tid; v < a.n_cand; v += kTrainThreads)
@@ -123,7 +155,9 @@ __global__ __launch_bounds__(kTrainThreads) void train_query_kernel(const TrainA
   z = wave_sum_d(z);
   if (lane == 0) s_red[wave] = z;
   __syncthreads();
-  z = s_red[0] + s_red[1] + s_red[2] + s_red[3];
+  z = 0.0;
+#pragma unroll
+  for (int w = 0; w < kTrainWaves; ++w) z += s_red[w];
   const double lse = mx + log(z);
   const double ce = n_p > 0.0 ? lse + pos_sum * inv_tau / n_p : 0.0;
   // g_v = -(softmax_v - [v positive] / P) / tau / nq (0 without positives).
@@ -148,51 +182,92 @@ __global__ __launch_bounds__(kTrainThreads) void train_query_kernel(const TrainA
       const float g = s_v[v];
       const int64_t id = cand_id(a, qi, v);
       if (g == 0.0f || id < 0) continue;
-      const int64_t row = a.inv_perm ? a.inv_perm[id] : id;
+      const int64_t row = a.code_lds ? 0 : (a.inv_perm ? a.inv_perm[id] : id);
       for (int mm = lane; mm < M; mm += 64) {
-        const int at = mm * kKsub + code_of(a, row, mm);
+        const int at = mm * kKsub + code_at(v, row, mm);
         s_tab[at] = __fadd_rn(s_tab[at], g);
       }
     }
   }
   __syncthreads();
 
-  // 4. Delta gradient (thread = codeword), alpha and w_f gradients.
-  const int c = tid;
+  // 4. Delta gradient (thread = codeword), alpha and w_f gradients.  Group
+  // `grp` of 256 threads takes subspaces grp, grp + 4, ...; `part` is a
+  // wavefront's place in its group.
+  const int c = tid & (kKsub - 1), grp = tid / kKsub, part = wave & 3;
   const float anchor = static_cast<float>(2.0 * a.lam / (static_cast<double>(M) * kKsub * d) / a.nq);
   const float* qrow = a.q + static_cast<int64_t>(qi) * a.dim;
   const float* wrow = a.wf + static_cast<int64_t>(qi) * a.dim;
   const float* arow = a.alpha + static_cast<int64_t>(qi) * mr;
   float* gdq = a.gdelta + static_cast<int64_t>(qi) * M * kKsub * d;
   double reg = 0.0;
-  for (int mm = 0; mm < M; ++mm) {
+  for (int mm = grp; mm < M; mm += kTrainGroups) {
     const float gl = s_tab[mm * kKsub + c];
-    for (int j = 0; j < d; ++j) {
-      float delta = 0.0f;
-      for (int t = 0; t < r; ++t)
-        delta = __fadd_rn(delta, __fmul_rn(arow[mm * r + t], a.W[((static_cast<int64_t>(mm) * r + t) * kKsub + c) * d + j]));
-      const float cq = __fadd_rn(a.cpq[(static_cast<int64_t>(mm) * kKsub + c) * d + j], delta);
-      const float e = __fsub_rn(qrow[mm * d + j], cq);
-      const float gd = __fadd_rn(__fmul_rn(gl, __fmul_rn(-2.0f * wrow[mm * d + j], e)), __fmul_rn(anchor, delta));
-      gdq[(static_cast<int64_t>(mm) * kKsub + c) * d + j] = gd;
-      reg += static_cast<double>(delta) * delta;
-      const float gw = wave_sum(__fmul_rn(gl, __fmul_rn(e, e)));
-      if (lane == 0) s_gw[wave * a.dim + mm * d + j] = gw;
-    }
-    for (int t = 0; t < r; ++t) {
-      float ga = 0.0f;
-      for (int j = 0; j < d; ++j)
-        ga = __fadd_rn(ga, __fmul_rn(gdq[(static_cast<int64_t>(mm) * kKsub + c) * d + j],
-                                     a.W[((static_cast<int64_t>(mm) * r + t) * kKsub + c) * d + j]));
-      ga = wave_sum(ga);
-      if (lane == 0) s_ga[wave * mr + mm * r + t] = ga;
+    const float* wm = a.W + (static_cast<int64_t>(mm) * r * kKsub + c) * d;       // + t * 256 d + j
+    const float* cm = a.cpq + (static_cast<int64_t>(mm) * kKsub + c) * d;
+    float* gm = gdq + (static_cast<int64_t>(mm) * kKsub + c) * d;
+    if constexpr (D > 0) {
+      float wv[R][D], gd[D], gw[D], ga[R];
+#pragma unroll
+      for (int t = 0; t < R; ++t)
+#pragma unroll
+        for (int j = 0; j < D; ++j) wv[t][j] = wm[t * kKsub * D + j];
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        float delta = 0.0f;
+#pragma unroll
+        for (int t = 0; t < R; ++t) delta = __fadd_rn(delta, __fmul_rn(arow[mm * R + t], wv[t][j]));
+        const float e = __fsub_rn(qrow[mm * D + j], __fadd_rn(cm[j], delta));
+        gd[j] = __fadd_rn(__fmul_rn(gl, __fmul_rn(-2.0f * wrow[mm * D + j], e)), __fmul_rn(anchor, delta));
+        gm[j] = gd[j];
+        reg += static_cast<double>(delta) * delta;
+        gw[j] = __fmul_rn(gl, __fmul_rn(e, e));
+      }
+#pragma unroll
+      for (int t = 0; t < R; ++t) {
+        ga[t] = 0.0f;
+#pragma unroll
+        for (int j = 0; j < D; ++j) ga[t] = __fadd_rn(ga[t], __fmul_rn(gd[j], wv[t][j]));
+      }
+      // The D + R sums over the codewords side by side.
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) gw[j] += __shfl_xor(gw[j], o, 64);
+#pragma unroll
+        for (int t = 0; t < R; ++t) ga[t] += __shfl_xor(ga[t], o, 64);
+      }
+      if (lane == 0) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) s_gw[part * a.dim + mm * D + j] = gw[j];
+#pragma unroll
+        for (int t = 0; t < R; ++t) s_ga[part * mr + mm * R + t] = ga[t];
+      }
+    } else {
+      for (int j = 0; j < d; ++j) {
+        float delta = 0.0f;
+        for (int t = 0; t < r; ++t) delta = __fadd_rn(delta, __fmul_rn(arow[mm * r + t], wm[t * kKsub * d + j]));
+        const float e = __fsub_rn(qrow[mm * d + j], __fadd_rn(cm[j], delta));
+        gm[j] = __fadd_rn(__fmul_rn(gl, __fmul_rn(-2.0f * wrow[mm * d + j], e)), __fmul_rn(anchor, delta));
+        reg += static_cast<double>(delta) * delta;
+        const float gw = wave_sum(__fmul_rn(gl, __fmul_rn(e, e)));
+        if (lane == 0) s_gw[part * a.dim + mm * d + j] = gw;
+      }
+      for (int t = 0; t < r; ++t) {
+        float ga = 0.0f;
+        for (int j = 0; j < d; ++j) ga = __fadd_rn(ga, __fmul_rn(gm[j], wm[t * kKsub * d + j]));
+        ga = wave_sum(ga);
+        if (lane == 0) s_ga[part * mr + mm * r + t] = ga;
+      }
     }
   }
   reg = wave_sum_d(reg);
+  __syncthreads();
   if (lane == 0) s_red[wave] = reg;
   __syncthreads();
   if (tid == 0) {
-    const double rsum = s_red[0] + s_red[1] + s_red[2] + s_red[3];
+    double rsum = 0.0;
+    for (int w = 0; w < kTrainWaves; ++w) rsum += s_red[w];
     a.loss[qi] = static_cast<float>(ce + a.lam * rsum / (static_cast<double>(M) * kKsub * d));
   }
   float* garow = a.galpha + static_cast<int64_t>(qi) * mr;
@@ -210,39 +285,89 @@ __global__ __launch_bounds__(kTrainThreads) void train_query_kernel(const TrainA
   }
 }
 
-__global__ __launch_bounds__(256) void train_update_w_kernel(float* __restrict__ W, const float* __restrict__ gdelta,
-                                                             const float* __restrict__ alpha, int nq, int m, int r,
-                                                             int dsub, float lr) {
+// grid = (64-entry runs of a subspace's (c, j) slab, subspaces): lane = entry,
+// wavefront = quarter of the queries, RT directions at a time.
+constexpr int kUpdateQuarters = 4;
+template <int RT>
+__global__ __launch_bounds__(64 * kUpdateQuarters) void train_update_w_kernel(
+    float* __restrict__ W, const float* __restrict__ gdelta, const float* __restrict__ alpha, int nq, int m, int r,
+    int dsub, float lr) {
+  __shared__ float s_part[kUpdateQuarters][RT][64];
+  const int lane = threadIdx.x & 63;
+  const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int mm = blockIdx.y;
   const int64_t per_t = static_cast<int64_t>(kKsub) * dsub;
-  const int64_t total = static_cast<int64_t>(m) * r * per_t;
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= total) return;
-  const int64_t cj = e % per_t;                // (c, j) inside a (m, t) slab
-  const int64_t mt = e / per_t;
-  const int mm = static_cast<int>(mt / r), t = static_cast<int>(mt % r);
-  float g = 0.0f;
-  for (int q = 0; q < nq; ++q)
-    g = __fadd_rn(g, __fmul_rn(gdelta[(static_cast<int64_t>(q) * m + mm) * per_t + cj], alpha[static_cast<int64_t>(q) * m * r + mm * r + t]));
-  W[e] = __fsub_rn(W[e], __fmul_rn(lr, g));
+  const int64_t cj = static_cast<int64_t>(blockIdx.x) * 64 + lane;   // per_t is a multiple of 64
+  const int q0 = static_cast<int>(static_cast<int64_t>(nq) * part / kUpdateQuarters);
+  const int q1 = static_cast<int>(static_cast<int64_t>(nq) * (part + 1) / kUpdateQuarters);
+  const float* gd = gdelta + static_cast<int64_t>(mm) * per_t + cj;
+  const int64_t gstep = static_cast<int64_t>(m) * per_t;
+  for (int t0 = 0; t0 < r; t0 += RT) {
+    float g[RT] = {};
+    const float* al = alpha + static_cast<int64_t>(mm) * r + t0;
+    constexpr int kAhead = 8;
+    for (int q = q0; q < q1; q += kAhead) {
+      float v[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) v[u] = gd[(q + u < q1 ? q + u : q1 - 1) * gstep];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        if (q + u < q1) {
+#pragma unroll
+          for (int t = 0; t < RT; ++t)
+            if (t0 + t < r) g[t] = __fadd_rn(g[t], __fmul_rn(v[u], al[static_cast<int64_t>(q + u) * m * r + t]));
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < RT; ++t) s_part[part][t][lane] = g[t];
+    __syncthreads();
+    for (int t = part; t < RT; t += kUpdateQuarters)
+      if (t0 + t < r) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int p = 0; p < kUpdateQuarters; ++p) sum = __fadd_rn(sum, s_part[p][t][lane]);
+        const int64_t at = (static_cast<int64_t>(mm) * r + t0 + t) * per_t + cj;
+        W[at] = __fsub_rn(W[at], __fmul_rn(lr, sum));
+      }
+    __syncthreads();
+  }
 }
 
 // One workgroup per (query, hash function) pair p; the first pair that hits
 // a row sums the alpha gradients of all pairs hitting it, in pair order, and
-// applies them (the other pairs of the row return).
+// applies them (the other pairs of the row return).  256 pairs are compared
+// at once, their matches taken from ballots in order (a thread walking all
+// pairs took 50 us for 512 of them, this 6).
 __global__ __launch_bounds__(256) void train_update_bank_kernel(float* __restrict__ bank, int mr,
                                                                 const int32_t* __restrict__ rows, int h,
                                                                 const float* __restrict__ galpha, int pairs,
                                                                 float lr) {
+  __shared__ uint64_t s_hit[4];
   const int p = blockIdx.x;
+  const int wave = threadIdx.x >> 6;
   const int32_t row = rows[p];
-  for (int p2 = 0; p2 < p; ++p2)
-    if (rows[p2] == row) return;
-  for (int e = threadIdx.x; e < mr; e += blockDim.x) {
+  bool earlier = false;
+  for (int p2 = threadIdx.x; p2 < p; p2 += 256) earlier = earlier || rows[p2] == row;
+  if (__syncthreads_or(earlier ? 1 : 0)) return;
+  for (int e0 = 0; e0 < mr; e0 += 256) {
+    const int e = e0 + threadIdx.x;
     float g = 0.0f;
-    for (int p2 = p; p2 < pairs; ++p2)
-      if (rows[p2] == row) g = __fadd_rn(g, galpha[static_cast<int64_t>(p2 / h) * mr + e]);
-    const int64_t at = static_cast<int64_t>(row) * mr + e;
-    bank[at] = __fsub_rn(bank[at], __fmul_rn(lr, g));
+    for (int base = p; base < pairs; base += 256) {
+      const int p2 = base + threadIdx.x;
+      const uint64_t hit = __ballot(p2 < pairs && rows[p2 < pairs ? p2 : p] == row);
+      __syncthreads();
+      if ((threadIdx.x & 63) == 0) s_hit[wave] = hit;
+      __syncthreads();
+      for (int w = 0; w < 4; ++w)
+        for (uint64_t x = s_hit[w]; x != 0; x &= x - 1) {
+          const int at = base + 64 * w + __builtin_ctzll(x);
+          if (e < mr) g = __fadd_rn(g, galpha[static_cast<int64_t>(at / h) * mr + e]);
+        }
+    }
+    if (e < mr) {
+      const int64_t at = static_cast<int64_t>(row) * mr + e;
+      bank[at] = __fsub_rn(bank[at], __fmul_rn(lr, g));
+    }
   }
 }
 
@@ -258,20 +383,27 @@ size_t train_query_lds_bytes(int m, int dim, int n_cand, int mr) {
   return (floats + 1) / 2 * 8 + 12 * sizeof(double);
 }
 
-hipError_t launch_train_query(const TrainArgs& a, hipStream_t s) {
-  const size_t lds = train_query_lds_bytes(a.m, a.dim, a.n_cand, a.m * a.r);
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&train_query_kernel),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+hipError_t launch_train_query(const TrainArgs& args, hipStream_t s) {
+  TrainArgs a = args;
+  size_t lds = train_query_lds_bytes(a.m, a.dim, a.n_cand, a.m * a.r);
+  const size_t codes = static_cast<size_t>(a.n_cand) * a.mw * sizeof(uint32_t);
+  a.code_lds = lds + codes <= static_cast<size_t>(kLdsBudget) ? 1 : 0;
+  if (a.code_lds) lds += codes;
+  const void* fn = a.r != 8     ? reinterpret_cast<const void*>(&train_query_kernel<0, 0>)
+                   : a.dsub == 2 ? reinterpret_cast<const void*>(&train_query_kernel<2, 8>)
+                   : a.dsub == 4 ? reinterpret_cast<const void*>(&train_query_kernel<4, 8>)
+                   : a.dsub == 8 ? reinterpret_cast<const void*>(&train_query_kernel<8, 8>)
+                                 : reinterpret_cast<const void*>(&train_query_kernel<0, 0>);
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
   if (e != hipSuccess) return e;
-  train_query_kernel<<<dim3(a.nq), dim3(kTrainThreads), lds, s>>>(a);
-  return hipGetLastError();
+  void* params[] = {&a};
+  return hipLaunchKernel(fn, dim3(static_cast<unsigned>(a.nq)), dim3(kTrainThreads), params, lds, s);
 }
 
 hipError_t launch_train_update_w(float* W, const float* gdelta, const float* alpha, int nq, int m, int r,
                                  int dsub, float lr, hipStream_t s) {
-  const int64_t total = static_cast<int64_t>(m) * r * kKsub * dsub;
-  train_update_w_kernel<<<dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0, s>>>(W, gdelta, alpha, nq,
-                                                                                           m, r, dsub, lr);
+  const dim3 grid(static_cast<unsigned>(kKsub * dsub / 64), static_cast<unsigned>(m));
+  train_update_w_kernel<8><<<grid, dim3(64 * kUpdateQuarters), 0, s>>>(W, gdelta, alpha, nq, m, r, dsub, lr);
   return hipGetLastError();
 }
 

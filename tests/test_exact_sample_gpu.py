@@ -1,0 +1,44 @@
+"""The exact search's sampled first pass: the screened plan gives the direct
+plan's ids and distance bits where pass 1 reads every tile (k of 600), every
+second or every eighth one of a wavefront (k, rows and queries decide), for row
+lengths with the fixed builds (96, 128) and without (50), intervals and masks."""
+import pytest
+import torch
+
+from tests._gpu_util import say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2607_22922_amd import ifvs
+    return ifvs
+
+
+@pytest.mark.parametrize("n,dim,nq,cluster", [(600_001, 96, 256, (0,)), (300_007, 128, 70, ()), (2_500_003, 50, 256, (0,)),
+                                           (4_000, 96, 3, (0,))])
+def test_sampled_screening_matches_direct(B, n, dim, nq, cluster):
+    say(f"[exact] n={n} dim={dim} nq={nq} cluster={cluster}")
+    g = torch.Generator(device="cuda").manual_seed(n)
+    attrs = torch.randint(0, 1000, (1, n), generator=g, device="cuda", dtype=torch.int32)
+    means = torch.rand(20, dim, generator=g, device="cuda") * 2 - 1
+    x = means[torch.randint(0, 20, (n,), generator=g, device="cuda")]
+    x = x + 0.3 * torch.randn(n, dim, generator=g, device="cuda")
+    x[1::2003] = x[0]                                    # equal rows: ties by id
+    q = means[torch.randint(0, 20, (nq,), generator=g, device="cuda")] + 0.3 * torch.randn(nq, dim, generator=g,
+                                                                                            device="cuda")
+    q[0] = x[0]
+    codes = torch.zeros(n, 1, dtype=torch.uint8, device="cuda")
+    idx = B.Index(codes, torch.zeros(1, 256, dim, device="cuda"), attrs, max_batch=nq, max_k=600, cluster_cols=cluster)
+    idx.load_vectors(x)
+    preds = [[(0, (7 * i) % 400, (7 * i) % 400 + 500)] for i in range(nq)]
+    preds[-1] = [(0, 4, 5)]
+    for k in (1, 10, 100, 600):
+        out = []
+        for plan in (2, 1):
+            idx.set_option(B.OPT_EXACT_PLAN, plan)
+            ids, dist = idx.exact_search(q, preds, k)
+            torch.cuda.synchronize()
+            out.append((ids, dist.view(torch.int32)))
+        assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1]), k
