@@ -163,10 +163,13 @@ __global__ __launch_bounds__(256) void lut_generic_kernel(
 template <int DSUB, int R, typename OutT>
 void launch_fixed(dim3 g, hipStream_t s, const float* q, int dim, int M, const float* cpq, const float* W,
                   const float* alpha, const float* wf, int nq, OutT* out, float* parts, StageDone done) {
-  if (parts)
-    lut_fixed_kernel<DSUB, R, OutT, true><<<g, dim3(256), 0, s>>>(q, dim, M, cpq, W, alpha, wf, nq, out, parts, done);
-  else
-    lut_fixed_kernel<DSUB, R, OutT><<<g, dim3(256), 0, s>>>(q, dim, M, cpq, W, alpha, wf, nq, out, nullptr, done);
+  if constexpr (DSUB == 2 || DSUB == 4 || DSUB == 8) {   // lut_emits_bound_parts
+    if (parts) {
+      lut_fixed_kernel<DSUB, R, OutT, true><<<g, dim3(256), 0, s>>>(q, dim, M, cpq, W, alpha, wf, nq, out, parts, done);
+      return;
+    }
+  }
+  lut_fixed_kernel<DSUB, R, OutT><<<g, dim3(256), 0, s>>>(q, dim, M, cpq, W, alpha, wf, nq, out, nullptr, done);
 }
 
 template <int DSUB, typename OutT>
@@ -191,10 +194,19 @@ void launch_typed(const float* q, int dim, int M, int dsub, int r, const float* 
   const dim3 g(M, (nq + kQueriesPerBlock - 1) / kQueriesPerBlock);
   const bool has_alpha = alpha != nullptr;
   bool launched = false;
+  // Every sub-dimension count whose slice of W fits the registers beside the
+  // sums (M = 21, d = 5, 37 queries in binary16: the generic kernel's loads in
+  // the innermost loop took 88 us).
   switch (dsub) {
+    case 1: launched = launch_fixed_r<1>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
     case 2: launched = launch_fixed_r<2>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
+    case 3: launched = launch_fixed_r<3>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
     case 4: launched = launch_fixed_r<4>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
+    case 5: launched = launch_fixed_r<5>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
+    case 6: launched = launch_fixed_r<6>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
+    case 7: launched = launch_fixed_r<7>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
     case 8: launched = launch_fixed_r<8>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
+    case 9: launched = launch_fixed_r<9>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
     default: break;
   }
   if (!launched)
