@@ -27,6 +27,7 @@
 #include <climits>
 #include <cmath>
 
+#include "exact_bound.h"
 #include "ifvs_internal.h"
 #include "topk_device.h"
 
@@ -134,14 +135,8 @@ __global__ __launch_bounds__(64) void exact_query_kernel(const float* __restrict
     }
     const double qnorm = sqrt(s2);
     const double X = static_cast<double>(__uint_as_float(*max_norm_bits));
-    // Each product of values rounded to nearest bf16 (relative error at most
-    // u_b) is within 2 u_b + u_b^2 of the exact one, so x.q is within that
-    // times |x| |q|, and 2 x.q within twice it.
-    const double u_b = 0x1p-9;
-    const double g = (4.0 * dim + 16.0) * 0x1p-23;    // fp32 sums of dim terms, generously
-    const double e = 2.0 * ((2.01 * u_b + g) * X * qnorm + g * (X + qnorm) * (X + qnorm)) + 1e-30;
     qn[p] = acc;
-    eps[p] = static_cast<float>(e * (1.0 + 0x1p-20));
+    eps[p] = exact_eps(dim, X, qnorm);
     cand_n[p] = 0;
   }
 }
