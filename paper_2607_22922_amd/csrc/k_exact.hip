@@ -174,7 +174,7 @@ struct QueryInfo {
 // interval has width 0).
 struct alignas(16) ScreenCell {
   uint32_t row0, width;
-  float bound;                  // pass 2: |x|^2 - 2 x.q of a candidate is at most this
+  float bound;                  // pass 2: rows whose |x|^2 - 2 x.q exceeds this are no candidates
   uint32_t resid;
 };
 
@@ -308,7 +308,9 @@ void exact_screen_kernel(const ScreenArgs a) {
       if (PASS == 1) {
         if (sel) run_min[i] = fminf(run_min[i], dd);
       } else {
-        hits |= (sel && dd <= cell.bound ? 1u : 0u) << i;
+        // (not `<=`: where |x|^2, |q|^2 or x.q overflow, dd or the bound is NaN,
+        // and the row has to be scored)
+        hits |= (sel && !(dd > cell.bound) ? 1u : 0u) << i;
       }
     }
     // (candidates are rare: one loop over the set bits instead of 16 inlined
@@ -346,7 +348,7 @@ void exact_screen_kernel(const ScreenArgs a) {
 // ---------------------------------------------------------------- threshold
 // One wavefront per query position: v_k = k-th smallest bin value, and the
 // candidate bound thr = v_k + 2 eps (+inf while fewer than k bins hold a
-// row).
+// row, NaN without a finite eps: neither leaves a row out).
 __global__ __launch_bounds__(64) void exact_threshold_kernel(const float* __restrict__ bins, int64_t n_bins, int k,
                                                              int kpl, const float* __restrict__ eps,
                                                              float* __restrict__ thr) {
@@ -359,7 +361,7 @@ __global__ __launch_bounds__(64) void exact_threshold_kernel(const float* __rest
   for (int64_t b = 0; b < n_bins; b += 64) {
     const int64_t i = b + lane;
     const float v = i < n_bins ? src[i] : __builtin_inff();
-    const bool ok = v < __builtin_inff();
+    const bool ok = fabsf(v) < __builtin_inff();       // (-inf: an overflowed sum, no bound)
     const uint64_t key = (static_cast<uint64_t>(ordered_bits(v)) << 32) | static_cast<uint32_t>(i);
     pool_push(pool, cnt, kth, key, ok && key < kth, k, kpl);
   }

@@ -50,3 +50,26 @@ def test_nearest_row_with_one_sided_rounding(B, dim, k):
     (ids, dist), (ids1, dist1) = both_plans(B, idx, q, [[(0, 0, n)]] * nq, k)
     assert bool((ids1[:, 0] == near).all())              # the direct plan: scored as defined
     assert torch.equal(ids, ids1) and torch.equal(dist, dist1)
+
+
+@pytest.mark.parametrize("dim", [50, 96])
+def test_sums_beyond_fp32(B, dim):
+    """Finite values whose |q|^2, |x|^2 or x.q overflow fp32: no row is left
+    out for an infinite or undefined screened value."""
+    say(f"[exact bound] overflow dim={dim}")
+    n, nq, k = 60_000, 36, 10
+    g = torch.Generator(device="cuda").manual_seed(dim)
+    x = torch.randn(n, dim, generator=g, device="cuda")
+    q = torch.randn(nq, dim, generator=g, device="cuda")
+    q[1] = 1e20                                          # |q|^2 overflows, every distance too
+    q[2, 0] = 2e19                                       # the same in one dimension
+    preds = [[(0, 0, n)]] * nq
+    for big in (False, True):
+        if big:                                          # rows whose own norm overflows, a query near them, the origin
+            x[777:30_000:997] = 3e18 * (1 + 0.001 * torch.randn(30, dim, generator=g, device="cuda"))
+            q[3], q[4], q[5] = 3e18, -3e18, 0.0
+        idx = exact_index(B, x, nq, k)
+        (ids, dist), (ids1, dist1) = both_plans(B, idx, q, preds, k)
+        assert bool((ids1 >= 0).all())
+        for i in range(nq):
+            assert torch.equal(ids[i], ids1[i]) and torch.equal(dist[i], dist1[i]), (big, i)
