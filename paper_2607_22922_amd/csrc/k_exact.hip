@@ -40,6 +40,14 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 constexpr int kExWaves = 8;        // wavefronts per screening workgroup
 constexpr int kExKC = 8;           // K steps (16 dims each) loaded per round
+// Row lengths of up to kExKeep K steps (128 dimensions) keep the query tile's
+// fragments and the next row tile's in registers: 8 VGPRs a step beside about
+// 60, which fills the 128 of sixteen wavefronts per CU at 8 steps (pass 2 then
+// spills five).  Longer rows load both in the loop.  4M rows, 256 queries of 10% / 50%, us
+// with the loads in the loop -> held: 16 dimensions 323 / 540 -> 314 / 417, 32:
+// 318 / 591 -> 283 / 537, 64: 352 / 639 -> 322 / 638, 112: 501 / 963 -> 459 /
+// 914, 128: 558 / 1096 -> 529 / 1073.
+constexpr int kExKeep = 8;
 
 // fp32 -> bf16 bits, round to nearest even (finite inputs).
 __device__ __forceinline__ uint32_t bf16_bits(float f) {
@@ -183,13 +191,13 @@ struct alignas(16) ScreenCell {
 // intervals); wavefront w takes the chunk's 32-row tiles w, w + 8, ...
 //
 // Bound by the row fragments' way from L2 and by the test of 16 (row, query)
-// cells a lane: the queries' fragments stay in registers (KS <= 6), the next
+// cells a lane: the queries' fragments stay in registers (kExKeep), the next
 // tile's rows are loaded while this one is tested, and a cell's test is one
 // 16-byte LDS read, a subtraction, a multiply-add and two comparisons.  10M x
 // 96 dimensions, 256 queries of 10%: pass 1 690 -> 123 us (an eighth of the
 // tiles), pass 2 820 -> 660 (3.3 GB of fragments, 5 TB/s).
 template <int PASS, int KS>
-__global__ __launch_bounds__(kExWaves * 64) __attribute__((amdgpu_waves_per_eu(KS == 6 ? 4 : 2)))
+__global__ __launch_bounds__(kExWaves * 64) __attribute__((amdgpu_waves_per_eu(KS > 0 && KS <= kExKeep ? 4 : 2)))
 void exact_screen_kernel(const ScreenArgs a) {
   __shared__ QueryInfo s_q[32];
   __shared__ ScreenCell s_cell[32];
@@ -246,7 +254,7 @@ void exact_screen_kernel(const ScreenArgs a) {
 #pragma unroll
   for (int i = 0; i < 16; ++i) run_min[i] = __builtin_inff();
   const uint4* a_frag = a.qb + static_cast<size_t>(qt) * ks * 64;
-  constexpr bool kKeepA = KS > 0 && KS <= 6;
+  constexpr bool kKeepA = KS > 0 && KS <= kExKeep;
   uint4 ka[kKeepA ? KS : 1];
   if constexpr (kKeepA) {
 #pragma unroll
@@ -581,8 +589,14 @@ hipError_t launch_exact_screen(const ExactScreen& e, int pass, hipStream_t s) {
   a.cand_cap = e.cand_cap;
   const void* fn = nullptr;
   switch (a.ks) {
-    case 6: fn = screen_symbol<6>(pass); break;      // 96 dims
-    case 8: fn = screen_symbol<8>(pass); break;      // 128 dims
+    case 1: fn = screen_symbol<1>(pass); break;
+    case 2: fn = screen_symbol<2>(pass); break;
+    case 3: fn = screen_symbol<3>(pass); break;
+    case 4: fn = screen_symbol<4>(pass); break;
+    case 5: fn = screen_symbol<5>(pass); break;
+    case 6: fn = screen_symbol<6>(pass); break;
+    case 7: fn = screen_symbol<7>(pass); break;
+    case 8: fn = screen_symbol<8>(pass); break;
     default: fn = screen_symbol<0>(pass); break;
   }
   const int n_qtiles = (e.nq + 31) / 32;

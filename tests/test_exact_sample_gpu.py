@@ -42,3 +42,26 @@ def test_sampled_screening_matches_direct(B, n, dim, nq, cluster):
             torch.cuda.synchronize()
             out.append((ids, dist.view(torch.int32)))
         assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1]), k
+
+
+@pytest.mark.parametrize("dim", [1, 16, 17, 33, 64, 65, 96, 97, 112, 113, 128, 129, 144])
+def test_every_build_matches_direct(B, dim):
+    """Row lengths on both sides of each count of 16-dimension steps with a
+    build of its own (1 to 8) and above them."""
+    say(f"[exact] dim={dim}")
+    n, nq, k = 50_003, 45, 10
+    g = torch.Generator(device="cuda").manual_seed(dim)
+    attrs = torch.randint(0, 1000, (1, n), generator=g, device="cuda", dtype=torch.int32)
+    x = torch.randn(n, dim, generator=g, device="cuda")
+    q = torch.randn(nq, dim, generator=g, device="cuda")
+    idx = B.Index(torch.zeros(n, 1, dtype=torch.uint8, device="cuda"), torch.zeros(1, 256, dim, device="cuda"), attrs,
+                  max_batch=nq, max_k=k, cluster_cols=(0,))
+    idx.load_vectors(x)
+    preds = [[(0, (7 * i) % 400, (7 * i) % 400 + 500)] for i in range(nq)]
+    out = []
+    for plan in (2, 1):
+        idx.set_option(B.OPT_EXACT_PLAN, plan)
+        ids, dist = idx.exact_search(q, preds, k)
+        torch.cuda.synchronize()
+        out.append((ids, dist.view(torch.int32)))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
