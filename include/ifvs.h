@@ -622,6 +622,16 @@ ifvs_status ifvs_probe_lds_gather(int32_t active_lanes, double* wave_reads_per_s
  * Errors: IFVS_E_INVALID (NULL out5), IFVS_E_STATE. */
 ifvs_status ifvs_last_plan(const ifvs_index* idx, int64_t* out5);
 
+/* ifvs_last_modes -- which path scored each query of the most recent filtered
+ * search on this index (for measurement and tests), after its stream has been
+ * synchronized: 0 the tiled scan (also queries that select nothing), 1 the
+ * compacted row list, 2 the packed-table screening, 3 the list scan.
+ *  nq:        at most that search's
+ *  modes_out: HOST [nq]
+ * Synchronous.  Errors: IFVS_E_INVALID (NULL modes_out, nq out of range),
+ * IFVS_E_STATE, IFVS_E_HIP. */
+ifvs_status ifvs_last_modes(const ifvs_index* idx, int32_t nq, int32_t* modes_out);
+
 /* Text of the last failure on the calling thread; valid until the next call
  * on this thread.  Never NULL. */
 const char* ifvs_last_error(void);

@@ -330,6 +330,8 @@ struct ifvs_index {
   StageTimer* timers = nullptr;  // [kStages] once profiling was enabled
   ScanPlan last_plan{};
   bool last_coarse = false;
+  int last_nq = 0;               // queries of the last filtered search
+  bool last_has_modes = false;   // qmode says which path scored each of them
 
   void free_vectors() {
     for (void* p : {static_cast<void*>(xt), static_cast<void*>(xr), static_cast<void*>(xb), static_cast<void*>(xn),
@@ -1718,6 +1720,8 @@ ifvs_status run_search(ifvs_index* idx, int32_t nq, const void* lut, int32_t lut
     lp.lds_bytes = list_scan_lds_bytes(idx->m, lut_dtype, pool_stride_for(k));
     idx->last_plan = lp;
     idx->last_coarse = true;
+    idx->last_nq = nq;
+    idx->last_has_modes = false;
     return IFVS_OK;
   }
   // Masked batches: a query whose pool is small is scored from its compacted
@@ -1835,6 +1839,8 @@ ifvs_status run_search(ifvs_index* idx, int32_t nq, const void* lut, int32_t lut
   }
   idx->last_plan = plan;
   idx->last_coarse = false;
+  idx->last_nq = nq;
+  idx->last_has_modes = mode != nullptr;
   return IFVS_OK;
 }
 
@@ -2483,6 +2489,20 @@ ifvs_status ifvs_last_coarse(const ifvs_index* idx, int32_t* used_out) {
   if (ifvs_status st = check_index(idx); st != IFVS_OK) return st;
   if (!used_out) return fail(IFVS_E_INVALID, "used_out is NULL");
   *used_out = idx->last_coarse ? 1 : 0;
+  return IFVS_OK;
+}
+
+ifvs_status ifvs_last_modes(const ifvs_index* idx, int32_t nq, int32_t* modes_out) {
+  if (ifvs_status st = check_index(idx); st != IFVS_OK) return st;
+  if (!modes_out) return fail(IFVS_E_INVALID, "modes_out is NULL");
+  if (nq < 0 || nq > idx->last_nq)
+    return fail(IFVS_E_INVALID, "nq exceeds the last search's " + std::to_string(idx->last_nq) + " queries");
+  if (idx->last_has_modes && nq > 0) {
+    IFVS_HIP(hipSetDevice(idx->device), "hipSetDevice");
+    IFVS_HIP(hipMemcpy(modes_out, idx->qmode, sizeof(int32_t) * nq, hipMemcpyDeviceToHost), "reading scan modes");
+    return IFVS_OK;
+  }
+  std::fill(modes_out, modes_out + nq, idx->last_coarse ? 3 : 0);
   return IFVS_OK;
 }
 

@@ -40,7 +40,7 @@ EXPORTED = ("ifvs_load_index", "ifvs_free_index", "ifvs_select_codebook", "ifvs_
             "ifvs_filtered_search_noalloc", "ifvs_read_scan_reads", "ifvs_probe_lds_gather",
             "ifvs_encoder_params", "ifvs_load_encoder", "ifvs_encode_predicates",
             "ifvs_build_coarse", "ifvs_lut_bounds", "ifvs_filtered_search_bounded", "ifvs_read_coarse",
-            "ifvs_last_coarse", "ifvs_query_batch")
+            "ifvs_last_coarse", "ifvs_last_modes", "ifvs_query_batch")
 
 
 class IfvsError(RuntimeError):
@@ -134,6 +134,7 @@ def _load_library() -> ctypes.CDLL:
         "ifvs_query_batch": ([vp, i32, vp, vp, vp, vp, vp, vp, i32, vp, i32, vp, vp, vp], i32),
         "ifvs_read_coarse": ([vp, ctypes.POINTER(i32), vp, vp, vp], i32),
         "ifvs_last_coarse": ([vp, ctypes.POINTER(i32)], i32),
+        "ifvs_last_modes": ([vp, i32, vp], i32),
     }
     for name, (args, res) in sig.items():
         fn = getattr(lib, name)
@@ -262,6 +263,13 @@ class Index:
         out = ctypes.c_int32()
         _check(_lib.ifvs_last_coarse(self.handle, ctypes.byref(out)))
         return bool(out.value)
+
+    def last_modes(self, nq: int):
+        """Which path scored each query of the most recent filtered search:
+        0 tiled scan, 1 row list, 2 screening, 3 list scan (host int32)."""
+        out = np.empty(nq, dtype=np.int32)
+        _check(_lib.ifvs_last_modes(self.handle, nq, out.ctypes.data))
+        return out
 
     def build_coarse(self, n_centroids: int, iters: int = 20) -> None:
         """ifvs_build_coarse: the coarse quantizer of the exact pruning bound."""

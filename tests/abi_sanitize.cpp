@@ -145,6 +145,7 @@ int main() {
          ifvs_query_batch(nullptr, 1, f, &pred, f, nullptr, f, f, 0, f, 1, i32, f, nullptr), IFVS_E_STATE);
   expect("read_coarse", ifvs_read_coarse(nullptr, i32, nullptr, nullptr, u8), IFVS_E_STATE);
   expect("last_coarse", ifvs_last_coarse(nullptr, i32), IFVS_E_STATE);
+  expect("last_modes", ifvs_last_modes(nullptr, 1, i32), IFVS_E_STATE);
   expect("load_vectors", ifvs_load_vectors(nullptr, f, IFVS_MEM_HOST), IFVS_E_STATE);
   expect("train_step",
          ifvs_train_step(nullptr, 1, f, &pred, f, i32, 1, 1, 1.0f, 0.0f, 0.1f, f, f, nullptr), IFVS_E_STATE);

@@ -54,12 +54,14 @@ def _both(B, idx, preds, lut, k, dt):
         idx.set_option(B.OPT_SCREEN, mode)
         ids, dist = idx.search(preds, lut, k, dt)
         torch.cuda.synchronize()
-        out.append((_np(ids), _np(dist)))
+        modes = idx.last_modes(len(preds))
+        out.append((_np(ids), _np(dist), modes))
     idx.set_option(B.OPT_SCREEN, 0)
-    (ids, dist), (ids1, dist1) = out
+    (ids, dist, modes), (ids1, dist1, modes1) = out
     assert np.array_equal(ids, ids1)
     assert np.array_equal(dist.view(np.uint32), dist1.view(np.uint32))
-    return ids, dist
+    assert not (modes1 == 2).any()                       # the tiled scan or row lists
+    return ids, dist, modes
 
 
 def _check(lut, codes, attrs, preds, k, ids, dist, rows):
@@ -83,8 +85,15 @@ def test_screening_matches_scan_and_oracle(B, n, m, nq, k, f16, cluster):
     lut = torch.rand(nq, m, 256, generator=g, device="cuda") ** 2 * 7 + 0.25 * torch.rand(nq, m, 1, generator=g, device="cuda")
     dt = B.LUT_F16 if f16 else B.LUT_F32
     lut = lut.half() if f16 else lut
-    ids, dist = _both(B, idx, preds, lut, k, dt)
+    idx.set_option(B.OPT_GATHER, 2)                      # no row lists: screened or left to the scan
+    ids, dist, modes = _both(B, idx, preds, lut, k, dt)
     _check(lut, codes, attrs, preds, k, ids, dist, range(min(nq, 13)))
+    for i, p in enumerate(preds):
+        rows = int(O.predicate_mask(attrs, p).sum())
+        if rows * min(1.0, 128 * 64 / n) >= 4 * k + 32:  # plenty in the seed's sample of 128 tiles
+            assert modes[i] == 2, (i, p, rows)
+        elif rows < k:
+            assert modes[i] == 0, (i, p, rows)
 
 
 def test_screening_leaves_unbounded_queries_to_the_scan(B):
@@ -102,25 +111,33 @@ def test_screening_leaves_unbounded_queries_to_the_scan(B):
     lut[7] *= 1e-38
     lut[8] *= 1e37
     lut[9, 2:] = 0.0
-    ids, dist = _both(B, idx, preds, lut, k, B.LUT_F32)
+    ids, dist, modes = _both(B, idx, preds, lut, k, B.LUT_F32)
     _check(lut, codes, attrs, preds, k, ids, dist, [0, 1, 3, 5, 6, 7, 8, 9, 10, 11])
+    left = [1, 2, 4, 5, 6]                               # negative, NaN, infinite, equal rows
+    assert (modes[left] == 0).all() and (modes[[0, 3, 10, 11]] == 2).all(), modes
 
 
 def test_screening_is_chosen_by_work_and_sharing(B):
-    """A large batch over the same rows is screened automatically; every way
-    of asking for the tiled scan gives the same answer."""
+    """A large batch over the same rows is screened automatically, a small one
+    and every way of asking for the tiled scan are not; the same answer."""
     n, m, nq, k = 400_000, 16, 256, 10
     say("[screen] automatic")
     idx, codes, attrs, rng = _index(B, n, m, nq, k, (), seed=9)
     preds = _preds(rng, nq, 200)
     lut = torch.rand(nq, m, 256, device="cuda", generator=torch.Generator(device="cuda").manual_seed(2)) ** 2
-    ids, dist = _both(B, idx, preds, lut, k, B.LUT_F32)
-    for opt, value in ((None, 0), (B.OPT_QTILE, 2), (B.OPT_GATHER, 2)):
+    ids, dist, _ = _both(B, idx, preds, lut, k, B.LUT_F32)
+    half = np.array([p[0][2] - p[0][1] > 1 and len(p) == 1 for p in preds])       # half of the rows
+    for opt, value in ((None, 0), (B.OPT_QTILE, 2), (B.OPT_GATHER, 2), (B.OPT_SCREEN, 1)):
         if opt:
             idx.set_option(opt, value)
         i2, d2 = idx.search(preds, lut, k)
         torch.cuda.synchronize()
+        modes = idx.last_modes(nq)
         if opt:
             idx.set_option(opt, 0)
         assert np.array_equal(_np(i2), ids) and np.array_equal(_np(d2).view(np.uint32), dist.view(np.uint32))
+        assert (modes[half] == (0 if opt in (B.OPT_QTILE, B.OPT_SCREEN) else 2)).all(), (opt, modes)
     _check(lut, codes, attrs, preds, k, ids, dist, range(0, nq, 41))
+    idx.search(preds[:8], lut[:8].contiguous(), k)                                # little to share
+    torch.cuda.synchronize()
+    assert not (idx.last_modes(8) == 2).any()
