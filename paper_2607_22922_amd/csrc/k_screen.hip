@@ -311,6 +311,12 @@ __global__ __launch_bounds__(kThreads) void screen_kernel(const ScreenBatch a) {
     const int cell_t0 = cell * cell_tiles;
     const int tb = max(t_lo, cell_t0), te = min(t_hi, cell_t0 + cell_tiles);
     int qc = 0;
+    // Queries whose list is full when this wavefront appends to it (bit i) are
+    // not screened any further: the scan takes them.  Without this a query of
+    // equal rows queues every one of them (16 such among 256 over 4M masked
+    // rows of 48-byte codes: 24.7 ms -> 8.8; asking at the start of a cell
+    // too costs the others 7-35%).
+    uint32_t over = 0;
     auto flush = [&]() {
       wave_lds_fence();
       for (int e0 = 0; e0 < qc; e0 += 64) {
@@ -324,6 +330,7 @@ __global__ __launch_bounds__(kThreads) void screen_kernel(const ScreenBatch a) {
           int base = 0;
           if (lane == 0) base = atomicAdd(&a.list_n[p], static_cast<int>(__popcll(mk)));
           base = __builtin_amdgcn_readfirstlane(base);
+          if (base + static_cast<int>(__popcll(mk)) > a.list_cap) over |= 1u << i;
           const int pos = base + lanes_below(mk);
           if (ok && (v >> 30) == static_cast<uint32_t>(i) && pos < a.list_cap)
             a.lists[static_cast<size_t>(p) * a.list_cap + pos] =
@@ -351,7 +358,7 @@ __global__ __launch_bounds__(kThreads) void screen_kernel(const ScreenBatch a) {
         uint64_t any = 0;
 #pragma unroll
         for (int i = 0; i < kScreenGroup; ++i) {
-          lm[i] = in ? tile_interval(t, r0[i], r1[i]) : 0ull;
+          lm[i] = in && !((over >> i) & 1) ? tile_interval(t, r0[i], r1[i]) : 0ull;
           if (bits[i] && lm[i] != 0) lm[i] &= bits[i][t];
           any |= lm[i];
         }
@@ -424,7 +431,7 @@ __global__ __launch_bounds__(kThreads) void screen_kernel(const ScreenBatch a) {
 #pragma unroll
       for (int i = 0; i < kScreenGroup; ++i) {
         const uint64_t al = __ballot(left[i] == 0);
-        if (al == 0) continue;
+        if (al == 0 || ((over >> i) & 1)) continue;
         const int cnt = __popcll(al);
         if (qc + cnt > kQueue) flush();
         if (left[i] == 0)

@@ -5,6 +5,8 @@ group of four; subspace counts on both sides of the prefetched code words (6)
 and of a word's four; k at its limit and above the rows selected; tables with
 negative, NaN and infinite entries, and lists that overflow (equal rows), which
 keep the tiled scan."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -141,3 +143,31 @@ def test_screening_is_chosen_by_work_and_sharing(B):
     idx.search(preds[:8], lut[:8].contiguous(), k)                                # little to share
     torch.cuda.synchronize()
     assert not (idx.last_modes(8) == 2).any()
+
+
+def test_equal_rows_cost_little_more_than_the_scan(B):
+    """Queries whose every row ties overflow their survivor lists and are left
+    to the scan: the screening gives them up early (it took five times the
+    scan's time while it counted every row)."""
+    n, m, nq, k = 2_000_000, 48, 256, 10
+    say("[screen] tied tables, time")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    codes = torch.randint(0, 256, (n, m), generator=g, device="cuda", dtype=torch.uint8)
+    attrs = torch.randint(0, 100, (1, n), generator=g, device="cuda", dtype=torch.int32)
+    idx = B.Index(codes, torch.zeros(m, 256, 1, device="cuda"), attrs, max_batch=nq, max_k=k)
+    preds = [[(0, i % 50, i % 50 + 50)] for i in range(nq)]
+    lut = torch.full((nq, m, 256), 0.25, device="cuda")
+    best = {}
+    for mode in (0, 1):
+        idx.set_option(B.OPT_SCREEN, mode)
+        for _ in range(4):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            ids, dist = idx.search(preds, lut, k)
+            torch.cuda.synchronize()
+            best[mode] = min(best.get(mode, 1e9), time.perf_counter() - t0)
+        assert not (idx.last_modes(nq) == 2).any()
+        want = torch.stack([torch.nonzero((attrs[0] >= p[0][1]) & (attrs[0] < p[0][2]))[:k, 0] for p in preds[:50]])
+        assert torch.equal(ids[:50].long(), want)
+    say(f"[screen] tied: {best[0] * 1e3:.2f} ms automatic, {best[1] * 1e3:.2f} ms without the screening")
+    assert best[0] < 2.5 * best[1]
