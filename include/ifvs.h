@@ -535,8 +535,10 @@ ifvs_status ifvs_encode_predicates(ifvs_index* idx, int32_t nq, const ifvs_predi
                                      instead of absolute cell c of the grid                 */
 #define IFVS_OPT_GATHER 6         /* masked batches: 0 automatic (queries selecting up to 30% of
                                      the rows, within the row-list capacity, are scored from
-                                     their compacted row list), 1 every query whose list fits,
-                                     2 never (every query takes the tiled scan)               */
+                                     their compacted row list; of a batch that IFVS_OPT_SCREEN 0
+                                     screens, those selecting up to 3% and, of the others, those
+                                     that the screening leaves), 1 every query whose list fits,
+                                     2 never (no row lists)                                   */
 #define IFVS_OPT_SLOT_ORDER 8     /* chunk-grid scans: 0 dispatch whole-cell slots first in cell
                                      order, then the others by decreasing estimated work (the
                                      last workgroups are short), 1 slots in index order       */

@@ -1733,18 +1733,13 @@ ifvs_status run_search(ifvs_index* idx, int32_t nq, const void* lut, int32_t lut
                       gather_supported(idx->m, lut_dtype) &&
                       static_cast<size_t>(idx->m) * kKsub * gather_lut + gather_lds_bytes(plan.pool_stride) <=
                           static_cast<size_t>(kLdsBudget);
-  if (gather) {
-    if (ifvs_status st = filter_into_workspace(idx, ws, p.host, nq, false, true, s); st != IFVS_OK) return st;
-    const int64_t auto_rows =
-        p.screen && idx->opt_screen == 0 ? idx->n * kScreenGatherPct / 100 : gather_auto_rows(idx);
-    const int64_t max_rows = idx->opt_gather == 1 ? ws.list_cap : std::min(ws.list_cap, auto_rows);
-    IFVS_LAUNCH(idx, kStFilter, s, "launching compaction kernel",
-                launch_compact(ws.bitmap, ws.stride64, ws.counts, ws.count_parts,
-                               filter_count_parts(idx->n), nq, max_rows, ws.list_cap, ws.lists,
-                               ws.list_n, ws.qmode, s));
-  } else if (need_bitmap) {
-    if (ifvs_status st = filter_into_workspace(idx, ws, p.host, nq, true, false, s); st != IFVS_OK) return st;
-  }
+  // Largest pools scored from a row list: of the queries that the screening
+  // leaves, and, before it, instead of being screened at all.
+  const int64_t list_rows = idx->opt_gather == 1 ? ws.list_cap : std::min(ws.list_cap, gather_auto_rows(idx));
+  const int64_t unscreened_rows =
+      idx->opt_gather == 1 || idx->opt_screen != 0 ? list_rows : std::min(list_rows, idx->n * kScreenGatherPct / 100);
+  if (gather || need_bitmap)
+    if (ifvs_status st = filter_into_workspace(idx, ws, p.host, nq, !gather, gather, s); st != IFVS_OK) return st;
   if (p.screen) {
     ScreenBatch sb{};
     sb.codes_t = idx->codes_t;
@@ -1759,7 +1754,8 @@ ifvs_status run_search(ifvs_index* idx, int32_t nq, const void* lut, int32_t lut
     sb.stride64 = ws.stride64;
     sb.perm = idx->perm;
     sb.k = k;
-    sb.gathered = gather;
+    sb.counts = gather ? ws.counts : nullptr;
+    sb.list_rows = unscreened_rows;
     sb.mode = idx->qmode;
     sb.gthr = ws.gthr;
     sb.seed_tiles = p.screen_seed;
@@ -1781,6 +1777,11 @@ ifvs_status run_search(ifvs_index* idx, int32_t nq, const void* lut, int32_t lut
     sb.dist_out = dist_out;
     IFVS_LAUNCH(idx, kStScan, s, "launching screening kernels", launch_screen(sb, lut_dtype, s));
   }
+  if (gather)
+    IFVS_LAUNCH(idx, kStFilter, s, "launching compaction kernel",
+                launch_compact(ws.bitmap, ws.stride64, ws.counts, ws.count_parts,
+                               filter_count_parts(idx->n), nq, list_rows, ws.list_cap, ws.lists,
+                               ws.list_n, ws.qmode, p.screen, s));
   const int32_t* mode = gather ? ws.qmode : (p.screen ? idx->qmode : nullptr);
   ScanBatch b{};
   b.codes_t = idx->codes_t;

@@ -284,7 +284,8 @@ hipError_t launch_rowmajor_codes(const uint32_t* codes_t, int64_t n, int mw, int
 // never) and, for those, the ascending list of selected physical rows.
 hipError_t launch_compact(const uint64_t* bitmap, int64_t stride64, const unsigned long long* counts,
                           const uint32_t* count_prefix, int64_t parts, int nq, int64_t max_rows,
-                          int64_t list_cap, int32_t* lists, int32_t* list_n, int32_t* mode, hipStream_t s);
+                          int64_t list_cap, int32_t* lists, int32_t* list_n, int32_t* mode, bool screened,
+                          hipStream_t s);
 hipError_t launch_gather_scan(const GatherBatch& b, hipStream_t s);
 
 hipError_t launch_scan(const ScanBatch& b, const ScanPlan& plan, hipStream_t s);
@@ -306,8 +307,9 @@ struct ScreenBatch {
   int64_t stride64;
   const int32_t* perm;
   int k;
-  bool gathered;                // mode holds 1 for queries the gather scan scores
-  int32_t* mode;                // [nq] out: 2 screened and answered, 0 left to the scan
+  const unsigned long long* counts;   // [nq] pool sizes: pools of at most list_rows rows are not
+  int64_t list_rows;                  //   screened (null: every query is)
+  int32_t* mode;                // [nq] out: 2 screened and answered, 0 not
   uint64_t* gthr;               // [nq] the scan's shared thresholds (the seed lowers them)
   int seed_tiles;               // tiles of a query's sample
   int levels;                   // L: packed units between the smallest possible distance and T

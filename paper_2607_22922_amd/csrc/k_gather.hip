@@ -44,7 +44,8 @@ __global__ void rowmajor_kernel(const uint32_t* __restrict__ codes_t, int64_t n,
   }
 }
 
-// mode[q] = 1 (gather) when the pool holds at most max_rows rows, and then
+// mode[q] = 1 (gather) when the pool holds at most max_rows rows and the
+// screening (when it ran) did not answer the query, and then
 // the ascending list of its selected physical rows.  Workgroup (g, q) covers
 // kCompactParts consecutive filter parts of query q (thread t: 4 consecutive
 // bitmap words); its rows start at the Filter stage's prefix count of its
@@ -52,12 +53,13 @@ __global__ void rowmajor_kernel(const uint32_t* __restrict__ codes_t, int64_t n,
 __global__ __launch_bounds__(kCompactThreads) void compact_kernel(
     const uint64_t* __restrict__ bitmap, int64_t stride64, const unsigned long long* __restrict__ counts,
     const uint32_t* __restrict__ count_prefix, int64_t parts, int nq, int64_t max_rows, int64_t list_cap,
-    int32_t* __restrict__ lists, int32_t* __restrict__ list_n, int32_t* __restrict__ mode) {
+    int32_t* __restrict__ lists, int32_t* __restrict__ list_n, int32_t* __restrict__ mode, int screened) {
   const int q = blockIdx.y;
   const int64_t part0 = static_cast<int64_t>(blockIdx.x) * kCompactParts;
   if (q >= nq || part0 >= parts) return;
   const unsigned long long cnt = counts[q];
   const bool gather = max_rows >= 0 && cnt <= static_cast<unsigned long long>(max_rows);
+  if (screened && mode[q] == 2) return;   // (only other values are written below)
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     mode[q] = gather ? 1 : 0;
     list_n[q] = gather ? static_cast<int32_t>(cnt) : 0;
@@ -329,10 +331,11 @@ hipError_t launch_rowmajor_codes(const uint32_t* codes_t, int64_t n, int mw, int
 
 hipError_t launch_compact(const uint64_t* bitmap, int64_t stride64, const unsigned long long* counts,
                           const uint32_t* count_prefix, int64_t parts, int nq, int64_t max_rows,
-                          int64_t list_cap, int32_t* lists, int32_t* list_n, int32_t* mode, hipStream_t s) {
+                          int64_t list_cap, int32_t* lists, int32_t* list_n, int32_t* mode, bool screened,
+                          hipStream_t s) {
   const dim3 grid(static_cast<unsigned>((parts + kCompactParts - 1) / kCompactParts), static_cast<unsigned>(nq));
   compact_kernel<<<grid, dim3(kCompactThreads), 0, s>>>(bitmap, stride64, counts, count_prefix, parts, nq,
-                                                         max_rows, list_cap, lists, list_n, mode);
+                                                         max_rows, list_cap, lists, list_n, mode, screened ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -129,11 +129,11 @@ __global__ __launch_bounds__(kSeedThreads) void screen_seed_kernel(const ScreenB
   if (threadIdx.x == 0) {
     a.list_n[p] = 0;
     a.level[p] = -1;
-    if (!a.gathered) a.mode[q] = 0;
+    a.mode[q] = 0;
     s_bad = 0;
     s_cut = 0xFFFFFFFFu;
   }
-  if (a.gathered && a.mode[q] == 1) return;   // scored by the gather scan
+  if (a.counts && a.counts[q] <= static_cast<unsigned long long>(a.list_rows)) return;   // left to the row lists
   const int64_t r0 = a.iv[2 * q], r1 = a.iv[2 * q + 1];
   if (r1 <= r0) return;                        // nothing selected: the scan writes the empty lists
   const bool resid = a.preds[q].residual_mask != 0;

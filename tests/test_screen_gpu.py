@@ -171,3 +171,31 @@ def test_equal_rows_cost_little_more_than_the_scan(B):
         assert torch.equal(ids[:50].long(), want)
     say(f"[screen] tied: {best[0] * 1e3:.2f} ms automatic, {best[1] * 1e3:.2f} ms without the screening")
     assert best[0] < 2.5 * best[1]
+
+
+def test_queries_left_by_the_screening_take_row_lists(B):
+    """A masked batch is screened before the row lists are made, so a pool of
+    up to 30% of the rows that the screening leaves (tied rows) is scored from
+    its list, as without the screening, and not by a pass over every tile."""
+    n, m, nq, k = 1_500_000, 48, 256, 10
+    say("[screen] row lists after the screening")
+    g = torch.Generator(device="cuda").manual_seed(4)
+    codes = torch.randint(0, 256, (n, m), generator=g, device="cuda", dtype=torch.uint8)
+    attrs = torch.randint(0, 100, (1, n), generator=g, device="cuda", dtype=torch.int32)
+    idx = B.Index(codes, torch.zeros(m, 256, 1, device="cuda"), attrs, max_batch=nq, max_k=k)
+    width = [(2, 10, 50)[i % 3] for i in range(nq)]                   # 2%, 10% and 50% of the rows
+    preds = [[(0, i % 50, i % 50 + w)] for i, w in enumerate(width)]
+    lut = torch.rand(nq, m, 256, device="cuda", generator=g) ** 2
+    tied = torch.arange(nq, device="cuda") % 5 == 0
+    lut[tied] = 0.25
+    out = []
+    for mode in (0, 1):
+        idx.set_option(B.OPT_SCREEN, mode)
+        ids, dist = idx.search(preds, lut, k)
+        torch.cuda.synchronize()
+        out.append((ids, dist.view(torch.int32), idx.last_modes(nq)))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    for i, w in enumerate(width):
+        want = 1 if w == 2 else (2 if not tied[i] else (1 if w == 10 else 0))
+        assert out[0][2][i] == want, (i, w, bool(tied[i]), out[0][2][i])
+        assert out[1][2][i] == (1 if w <= 10 else 0)
