@@ -803,8 +803,12 @@ ifvs_status timed(ifvs_index* idx, int stage, hipStream_t s, const char* what, F
 // Largest pool (rows) the automatic mode scores from a row list.
 int64_t gather_auto_rows(const ifvs_index* idx) { return idx->n * idx->opt_gather_auto_pct / 100; }
 
-// fallback: the scan only serves queries the screening leaves (usually none):
-// equal chunks, few of them, so that the empty launch is short.
+// fallback: the scan only serves queries the screening leaves, usually none.
+// The chunk grid's empty workgroups would cost every batch (100M rows, 256
+// queries: 2478 -> 2545 us), so long spans are cut into equal chunks, as many
+// as give about 8192 workgroups and at most 32 a query: one tied query of 256
+// over half of 10M 16-byte codes takes 4.1 ms, 8.4 in 16 chunks, 6.2 on the
+// grid (6.6 without the screening); 256 of them 22.7, 23.4 and 25.4 (24.0).
 // interval_batch: every query has a cluster-key interval; one query per tile
 // then keeps all lanes busy and the scan is bound by LDS lookups, so sharing
 // code tiles across queries would not help.  Otherwise (masked rows) tiles
@@ -875,8 +879,10 @@ ifvs_status plan_scan(const ifvs_index* idx, int32_t nq, int32_t k, int32_t lut_
       splits = (idx->n_tiles + plan->chunk_tiles - 1) / plan->chunk_tiles;
     else if (plan->chunk_tiles > 0)
       splits = (span_tiles + plan->chunk_tiles - 1) / plan->chunk_tiles + 1;
+    else if (fallback && span_tiles >= 8192)
+      splits = std::max<int64_t>(std::min<int64_t>(16, (span_tiles + 8191) / 8192), std::min<int64_t>(32, 8192 / gy));
     else
-      splits = std::min<int64_t>(span_tiles >= 8192 && !fallback ? many_splits : 16,
+      splits = std::min<int64_t>(span_tiles >= 8192 ? many_splits : 16,
                                  std::max<int64_t>((span_tiles + 8191) / 8192, (512 + gy - 1) / gy));
   }
   if (idx->opt_splits > 0) splits = idx->opt_splits;

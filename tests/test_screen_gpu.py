@@ -157,20 +157,48 @@ def test_equal_rows_cost_little_more_than_the_scan(B):
     idx = B.Index(codes, torch.zeros(m, 256, 1, device="cuda"), attrs, max_batch=nq, max_k=k)
     preds = [[(0, i % 50, i % 50 + 50)] for i in range(nq)]
     lut = torch.full((nq, m, 256), 0.25, device="cuda")
-    best = {}
+    best = _times(B, idx, preds, lut, k, attrs, left=range(nq))
+    assert best[0] < 2.5 * best[1]
+
+
+def _times(B, idx, preds, lut, k, attrs, left):
+    """Seconds of a search with and without the screening; `left`: the queries
+    it must leave, whose rows all tie (the first k selected ids)."""
+    nq, best = len(preds), {}
+    pc = B.pack_predicates(preds)
+    ids = torch.empty(nq, k, dtype=torch.int32, device="cuda")
+    dist = torch.empty(nq, k, device="cuda")
     for mode in (0, 1):
         idx.set_option(B.OPT_SCREEN, mode)
         for _ in range(4):
             torch.cuda.synchronize()
             t0 = time.perf_counter()
-            ids, dist = idx.search(preds, lut, k)
+            idx.search_into(nq, pc, lut, B.LUT_F32, k, ids, dist)
             torch.cuda.synchronize()
             best[mode] = min(best.get(mode, 1e9), time.perf_counter() - t0)
-        assert not (idx.last_modes(nq) == 2).any()
-        want = torch.stack([torch.nonzero((attrs[0] >= p[0][1]) & (attrs[0] < p[0][2]))[:k, 0] for p in preds[:50]])
-        assert torch.equal(ids[:50].long(), want)
+        modes = idx.last_modes(nq) == 2
+        assert modes.any() == (mode == 0 and len(left) < nq) and not modes[list(left)].any()
+        for i in list(left)[:50]:
+            (_, lo, hi), = preds[i]
+            assert torch.equal(ids[i].long(), torch.nonzero((attrs[0] >= lo) & (attrs[0] < hi))[:k, 0])
     say(f"[screen] tied: {best[0] * 1e3:.2f} ms automatic, {best[1] * 1e3:.2f} ms without the screening")
-    assert best[0] < 2.5 * best[1]
+    return best
+
+
+def test_a_tied_query_over_a_long_interval(B):
+    """The scan of a query that the screening leaves is cut into chunks enough
+    for one query (in 16 it took longer than the whole batch's scan)."""
+    n, m, nq, k = 10_000_000, 16, 256, 10
+    say("[screen] one tied query over a long interval, time")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    codes = torch.randint(0, 256, (n, m), generator=g, device="cuda", dtype=torch.uint8)
+    attrs = torch.randint(0, 1000, (1, n), generator=g, device="cuda", dtype=torch.int32)
+    idx = B.Index(codes, torch.zeros(m, 256, 1, device="cuda"), attrs, max_batch=nq, max_k=k, cluster_cols=(0,))
+    preds = [[(0, i % 500, i % 500 + 500)] for i in range(nq)]
+    lut = torch.rand(nq, m, 256, device="cuda", generator=g) ** 2
+    lut[3] = 0.25
+    best = _times(B, idx, preds, lut, k, attrs, left=[3])
+    assert best[0] < 1.05 * best[1]
 
 
 def test_queries_left_by_the_screening_take_row_lists(B):
