@@ -260,7 +260,7 @@ struct ifvs_index {
   int32_t* list_n = nullptr;     // [max_batch]
   int32_t* qmode = nullptr;      // [max_batch] 1: gather scan
   int64_t list_cap = 0;
-  // Packed-table screening (null tab: no workspace).
+  // Packed-table screening (alloc_screen; one allocation, null: none).
   uint32_t* scr_tab = nullptr;   // [ceil(scr_batch / kScreenGroup)][mw * 4][256]
   int32_t* scr_lists = nullptr;  // [scr_batch][scr_cap] survivors
   float* scr_f = nullptr;        // [scr_batch][mw * 4 + 2] smallest entries, bounds, scales
@@ -367,8 +367,7 @@ struct ifvs_index {
                     static_cast<void*>(perm), static_cast<void*>(bank), static_cast<void*>(W),
                     static_cast<void*>(preds_dev), static_cast<void*>(qorder_dev),
                     static_cast<void*>(iv_dev), static_cast<void*>(gthr_dev), static_cast<void*>(bitmap),
-                    static_cast<void*>(scr_tab), static_cast<void*>(scr_lists), static_cast<void*>(scr_f),
-                    static_cast<void*>(scr_i),
+                    static_cast<void*>(scr_tab),
                     static_cast<void*>(bound_parts),
                     static_cast<void*>(slot_order_dev),
                     static_cast<void*>(counts), static_cast<void*>(count_parts), static_cast<void*>(vstart),
@@ -406,6 +405,23 @@ ifvs_status dev_alloc(T** p, size_t count, const char* what) {
     return fail(IFVS_E_NOMEM, std::string("device allocation failed: ") + what);
   }
   return IFVS_OK;
+}
+
+// The screening's workspace, one allocation: packed tables, survivor lists of
+// up to 32768 rows a query (256 MiB for the batch), bounds and counts.  Where
+// it cannot be had the index goes without (null scr_tab).
+void alloc_screen(ifvs_index* idx) {
+  if (idx->scr_tab || !screen_supported(idx->m, 1)) return;
+  const int batch = std::min(idx->max_batch, kScreenBatch);
+  const size_t nb = static_cast<size_t>(batch), groups = (nb + kScreenGroup - 1) / kScreenGroup;
+  const int cap = static_cast<int>(std::min<int64_t>({32768, (int64_t{64} << 20) / batch, idx->n}));
+  const size_t tab = groups * idx->mw * 4 * kKsub, lists = nb * cap, f = nb * (idx->mw * 4 + 2);
+  if (dev_alloc(&idx->scr_tab, tab + lists + f + nb * 2, "screening workspace") != IFVS_OK) return;
+  idx->scr_lists = reinterpret_cast<int32_t*>(idx->scr_tab + tab);
+  idx->scr_f = reinterpret_cast<float*>(idx->scr_lists + lists);
+  idx->scr_i = reinterpret_cast<int32_t*>(idx->scr_f + f);
+  idx->scr_batch = batch;
+  idx->scr_cap = cap;
 }
 
 // Device memory one filtered search works in: the index's workspace, or, for
@@ -1133,17 +1149,6 @@ ifvs_status ifvs_load_index(const ifvs_index_desc* desc, ifvs_index** out) {
       return bail(st);
   }
   if ((st = dev_alloc(&idx->qmode, static_cast<size_t>(d.max_batch), "scan modes")) != IFVS_OK) return bail(st);
-  // Screening workspace: survivor lists of up to 32768 rows a query, 256 MiB
-  // for the batch.
-  if (screen_supported(d.m, 1)) {
-    idx->scr_batch = std::min(d.max_batch, kScreenBatch);
-    const size_t nb = static_cast<size_t>(idx->scr_batch), groups = (nb + kScreenGroup - 1) / kScreenGroup;
-    idx->scr_cap = static_cast<int>(std::min<int64_t>({32768, (int64_t{64} << 20) / idx->scr_batch, d.n}));
-    if ((st = dev_alloc(&idx->scr_tab, groups * idx->mw * 4 * kKsub, "packed tables")) != IFVS_OK) return bail(st);
-    if ((st = dev_alloc(&idx->scr_lists, nb * idx->scr_cap, "survivor lists")) != IFVS_OK) return bail(st);
-    if ((st = dev_alloc(&idx->scr_f, nb * (idx->mw * 4 + 2), "screening bounds")) != IFVS_OK) return bail(st);
-    if ((st = dev_alloc(&idx->scr_i, nb * 2, "survivor counts")) != IFVS_OK) return bail(st);
-  }
   const size_t cb = static_cast<size_t>(d.m) * kKsub * idx->dsub;
   if ((st = dev_alloc(&idx->cpq, cb, "codebook")) != IFVS_OK) return bail(st);
   if (hipError_t e = hipMemcpy(idx->cpq, d.codebook, cb * sizeof(float), kind); e != hipSuccess)
@@ -1228,6 +1233,8 @@ ifvs_status ifvs_load_index(const ifvs_index_desc* desc, ifvs_index** out) {
     idx->partial_keys = per_chunk * chunks;
     if ((st = dev_alloc(&idx->partials, idx->partial_keys, "top-k partials")) != IFVS_OK) return bail(st);
   }
+  // (last, and not needed: without it no batch is screened)
+  alloc_screen(idx);
   if (hipError_t e = hipDeviceSynchronize(); e != hipSuccess) return bail(hip_fail(e, "finishing load"));
   *out = idx;
   return IFVS_OK;

@@ -5,6 +5,9 @@ group of four; subspace counts on both sides of the prefetched code words (6)
 and of a word's four; k at its limit and above the rows selected; tables with
 negative, NaN and infinite entries, and lists that overflow (equal rows), which
 keep the tiled scan."""
+import os
+import subprocess
+import sys
 import time
 
 import numpy as np
@@ -15,6 +18,7 @@ import oracle as O
 from tests._gpu_util import check_search_row, say
 
 pytestmark = pytest.mark.gpu
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.fixture(scope="module")
@@ -227,3 +231,45 @@ def test_queries_left_by_the_screening_take_row_lists(B):
         want = 1 if w == 2 else (2 if not tied[i] else (1 if w == 10 else 0))
         assert out[0][2][i] == want, (i, w, bool(tied[i]), out[0][2][i])
         assert out[1][2][i] == (1 if w <= 10 else 0)
+
+
+LOAD_WITHOUT = r"""
+import sys, torch
+sys.path.insert(0, %r)
+from paper_2607_22922_amd import ifvs as B
+g = torch.Generator(device="cuda").manual_seed(1)
+n, m, nq, k = 5000, 4, 8, 5
+codes = torch.randint(0, 256, (n, m), generator=g, device="cuda", dtype=torch.uint8)
+attrs = torch.arange(n, device="cuda", dtype=torch.int32)[None].contiguous()
+lut = torch.rand(nq, m, 256, generator=g, device="cuda")
+preds = [[(0, 10 * i, 3000 + 10 * i)] for i in range(nq)]
+out = []
+for _ in range(2):
+    try:
+        idx = B.Index(codes, torch.zeros(m, 256, 1, device="cuda"), attrs, max_batch=nq, max_k=k)
+    except B.IfvsError as e:
+        print("REFUSED", e)
+        sys.exit(0)
+    print("LOADED", B.lib().ifvs_last_error().decode())
+    idx.set_option(B.OPT_SCREEN, 2)
+    ids, dist = idx.search(preds, lut, k)
+    torch.cuda.synchronize()
+    print("SCREENED", int((idx.last_modes(nq) == 2).sum()))
+    out.append((ids, dist))
+print("SAME", torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1]))
+"""
+
+
+def test_index_loads_without_the_screening_workspace():
+    """The workspace is the load's last allocation; when it fails, the index
+    loads all the same and its batches take the scan."""
+    for n in range(32, 0, -1):
+        p = subprocess.run([sys.executable, "-c", LOAD_WITHOUT % ROOT], capture_output=True, text=True, timeout=100,
+                           env=dict(os.environ, IFVS_FAIL_ALLOC=str(n)))
+        assert p.returncode == 0, p.stderr[-2000:]
+        say(f"[screen] allocation {n} fails: {p.stdout.split(chr(10))}")
+        lines = p.stdout.splitlines()
+        if "forced allocation failure" in lines[0]:
+            break
+    assert lines[0] == "LOADED forced allocation failure: screening workspace", lines
+    assert lines[1:] == ["SCREENED 0", lines[0], "SCREENED 8", "SAME True"], lines
