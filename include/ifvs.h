@@ -568,8 +568,11 @@ ifvs_status ifvs_encode_predicates(ifvs_index* idx, int32_t nq, const ifvs_predi
 #define IFVS_OPT_SCREEN 14       /* searches without the list scan: 0 automatic (large batches whose
                                     queries select largely the same rows are screened, four
                                     queries per table read, before their survivors are scored),
-                                    1 never, 2 whenever supported; the same results.  Forcing
-                                    an option of the tiled scan keeps the tiled scan.         */
+                                    1 never, 2 whenever supported (allocates the workspace of up
+                                    to 256 MiB of survivor lists and the packed tables, which a
+                                    load does where 0 can need them; without room for it no
+                                    batch is screened); the same results.  Forcing an option
+                                    of the tiled scan keeps the tiled scan.                   */
 #define IFVS_OPT_COUNT_READS 12  /* measurement only: 1 = scans run a build of the scan kernel
                                      that also counts its table reads (one per subspace and
                                      wavefront instruction, and one per coarse-bound lookup)

@@ -301,7 +301,8 @@ struct ifvs_index {
   // the planner estimate each query's interval length without touching the
   // device.
   std::vector<int32_t> fence0, fence1;
-  // [n_attr] kAttrSample evenly spaced values of each column, sorted.
+  // [n_attr] up to kAttrSample evenly spaced values of each column, sorted
+  // (empty where no masked batch is screened automatically).
   std::vector<std::vector<int32_t>> attr_sample;
 
   int opt_qtile = 0, opt_splits = 0, opt_min_chunk = 0;
@@ -422,6 +423,33 @@ void alloc_screen(ifvs_index* idx) {
   idx->scr_i = reinterpret_cast<int32_t*>(idx->scr_f + f);
   idx->scr_batch = batch;
   idx->scr_cap = cap;
+}
+
+// Whether a batch of this index can be screened automatically (plan_screen);
+// others get the workspace when IFVS_OPT_SCREEN asks for it.  Loading 10K rows
+// of 16-byte codes takes 0.18 ms, with the workspace and the samples 0.54.
+bool screen_reachable(const ifvs_index* idx) {
+  const bool fixed_m = idx->m == 16 || idx->m == 48 || idx->m == 120;
+  const int64_t least = fixed_m ? std::min(kScreenAutoWork, kScreenAutoWorkMasked)
+                                : std::min(kScreenAutoWorkAnyM, kScreenAutoWorkAnyMasked);
+  return std::min(idx->max_batch, kScreenBatch) * idx->n_tiles * idx->m >= least;
+}
+
+// Evenly spaced values of every column, sorted, by way of the survivor lists.
+hipError_t sample_attributes(ifvs_index* idx) {
+  const int64_t room = static_cast<int64_t>(idx->scr_batch) * idx->scr_cap / idx->n_attr;
+  const int per = static_cast<int>(std::min<int64_t>({idx->n, kAttrSample, room}));
+  std::vector<int32_t> host(static_cast<size_t>(idx->n_attr) * per);
+  hipError_t e = launch_sample_attrs(idx->attrs, idx->n, idx->n_attr, per, idx->scr_lists, nullptr);
+  if (e == hipSuccess)
+    e = hipMemcpy(host.data(), idx->scr_lists, host.size() * sizeof(int32_t), hipMemcpyDeviceToHost);
+  if (e != hipSuccess) return e;
+  for (int c = 0; c < idx->n_attr; ++c) {
+    idx->attr_sample.emplace_back(host.begin() + static_cast<int64_t>(c) * per,
+                                  host.begin() + static_cast<int64_t>(c + 1) * per);
+    std::sort(idx->attr_sample.back().begin(), idx->attr_sample.back().end());
+  }
+  return hipSuccess;
 }
 
 // Device memory one filtered search works in: the index's workspace, or, for
@@ -1058,21 +1086,6 @@ ifvs_status ifvs_load_index(const ifvs_index_desc* desc, ifvs_index** out) {
       return bail(hip_fail(e, "loading attributes"));
   }
   idx->attrs_phys = idx->attrs;
-  if (d.n_attr > 0) {
-    const int per = static_cast<int>(std::min<int64_t>(d.n, kAttrSample));
-    int32_t* dev = nullptr;
-    if ((st = dev_alloc(&dev, static_cast<size_t>(d.n_attr) * per, "attribute samples")) != IFVS_OK) return bail(st);
-    std::vector<int32_t> host(static_cast<size_t>(d.n_attr) * per);
-    hipError_t e = launch_sample_attrs(idx->attrs, d.n, d.n_attr, per, dev, nullptr);
-    if (e == hipSuccess) e = hipMemcpy(host.data(), dev, host.size() * sizeof(int32_t), hipMemcpyDeviceToHost);
-    hipFree(dev);
-    if (e != hipSuccess) return bail(hip_fail(e, "sampling attributes"));
-    for (int c = 0; c < d.n_attr; ++c) {
-      idx->attr_sample.emplace_back(host.begin() + static_cast<int64_t>(c) * per,
-                                    host.begin() + static_cast<int64_t>(c + 1) * per);
-      std::sort(idx->attr_sample.back().begin(), idx->attr_sample.back().end());
-    }
-  }
   if (d.n_cluster > 0) {
     if ((st = dev_alloc(&idx->perm, static_cast<size_t>(d.n), "cluster permutation")) != IFVS_OK) return bail(st);
     if (hipError_t e = cluster_permutation(idx->attrs, d.n, d.n_cluster, idx->c0, idx->c1, idx->perm, nullptr);
@@ -1234,7 +1247,9 @@ ifvs_status ifvs_load_index(const ifvs_index_desc* desc, ifvs_index** out) {
     if ((st = dev_alloc(&idx->partials, idx->partial_keys, "top-k partials")) != IFVS_OK) return bail(st);
   }
   // (last, and not needed: without it no batch is screened)
-  alloc_screen(idx);
+  if (screen_reachable(idx)) alloc_screen(idx);
+  if (idx->scr_tab && idx->codes_rm && d.n_attr > 0)
+    if (hipError_t e = sample_attributes(idx); e != hipSuccess) return bail(hip_fail(e, "sampling attributes"));
   if (hipError_t e = hipDeviceSynchronize(); e != hipSuccess) return bail(hip_fail(e, "finishing load"));
   *out = idx;
   return IFVS_OK;
@@ -1261,6 +1276,10 @@ ifvs_status ifvs_set_option(ifvs_index* idx, int32_t option, int64_t value) {
     case IFVS_OPT_SCREEN:
       if (value > 2) return fail(IFVS_E_INVALID, "IFVS_OPT_SCREEN takes 0, 1 or 2");
       idx->opt_screen = static_cast<int>(value);
+      if (value == 2) {
+        IFVS_HIP(hipSetDevice(idx->device), "hipSetDevice");
+        alloc_screen(idx);
+      }
       return IFVS_OK;
     case IFVS_OPT_SLOT_ORDER:
       if (value > 1) return fail(IFVS_E_INVALID, "IFVS_OPT_SLOT_ORDER takes 0 or 1");
@@ -1471,6 +1490,7 @@ void plan_screen(const ifvs_index* idx, int32_t nq, int32_t k, const DevPred* ho
     return;
   int64_t sum_iv = 0, sum_hull = 0, max_hull = 1, served = 0;
   const bool gather_able = automatic && masked && idx->codes_rm && idx->opt_gather != 2;
+  if (gather_able && static_cast<int>(idx->attr_sample.size()) < idx->n_attr) return;
   double otherwise_us = 0.0;   // masked: what the served queries would take in the gather or the tiled scan
   // At most 16 groups are looked at, evenly spaced (the sums scaled up): the
   // planning of a batch stays within a few microseconds.

@@ -238,20 +238,21 @@ import sys, torch
 sys.path.insert(0, %r)
 from paper_2607_22922_amd import ifvs as B
 g = torch.Generator(device="cuda").manual_seed(1)
-n, m, nq, k = 5000, 4, 8, 5
+n, m, nq, k, cluster, force = %s
 codes = torch.randint(0, 256, (n, m), generator=g, device="cuda", dtype=torch.uint8)
 attrs = torch.arange(n, device="cuda", dtype=torch.int32)[None].contiguous()
 lut = torch.rand(nq, m, 256, generator=g, device="cuda")
-preds = [[(0, 10 * i, 3000 + 10 * i)] for i in range(nq)]
+preds = [[(0, 10 * i, 10 * i + n - 1000)] for i in range(nq)]
 out = []
 for _ in range(2):
     try:
-        idx = B.Index(codes, torch.zeros(m, 256, 1, device="cuda"), attrs, max_batch=nq, max_k=k)
+        idx = B.Index(codes, torch.zeros(m, 256, 1, device="cuda"), attrs, max_batch=nq, max_k=k, cluster_cols=cluster)
     except B.IfvsError as e:
         print("REFUSED", e)
         sys.exit(0)
+    if force:
+        idx.set_option(B.OPT_SCREEN, 2)
     print("LOADED", B.lib().ifvs_last_error().decode())
-    idx.set_option(B.OPT_SCREEN, 2)
     ids, dist = idx.search(preds, lut, k)
     torch.cuda.synchronize()
     print("SCREENED", int((idx.last_modes(nq) == 2).sum()))
@@ -260,16 +261,44 @@ print("SAME", torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1
 """
 
 
-def test_index_loads_without_the_screening_workspace():
-    """The workspace is the load's last allocation; when it fails, the index
-    loads all the same and its batches take the scan."""
-    for n in range(32, 0, -1):
-        p = subprocess.run([sys.executable, "-c", LOAD_WITHOUT % ROOT], capture_output=True, text=True, timeout=100,
-                           env=dict(os.environ, IFVS_FAIL_ALLOC=str(n)))
+@pytest.mark.parametrize("shape", [(5000, 4, 8, 5, (), True), (130_003, 4, 64, 5, (0,), False)],
+                         ids=["forced", "automatic"])
+def test_index_works_without_the_screening_workspace(shape):
+    """The workspace is the last allocation, of the load where batches can be
+    screened automatically, else of asking for it; when it fails, the index
+    works all the same and its batches take the scan."""
+    nq = shape[2]
+    for n in range(34, 0, -1):
+        p = subprocess.run([sys.executable, "-c", LOAD_WITHOUT % (ROOT, shape)], capture_output=True, text=True,
+                           timeout=100, env=dict(os.environ, IFVS_FAIL_ALLOC=str(n)))
         assert p.returncode == 0, p.stderr[-2000:]
-        say(f"[screen] allocation {n} fails: {p.stdout.split(chr(10))}")
         lines = p.stdout.splitlines()
+        say(f"[screen] allocation {n} fails: {lines}")
         if "forced allocation failure" in lines[0]:
             break
     assert lines[0] == "LOADED forced allocation failure: screening workspace", lines
-    assert lines[1:] == ["SCREENED 0", lines[0], "SCREENED 8", "SAME True"], lines
+    assert lines[1:] == ["SCREENED 0", lines[0], f"SCREENED {nq}", "SAME True"], lines
+
+
+def test_small_index_takes_no_screening_workspace(B):
+    """No batch of it is screened automatically: the workspace is allocated
+    when the screening is asked for."""
+    n, m, nq, k = 1000, 16, 4096, 2
+    say("[screen] small index")
+    codes = torch.randint(0, 256, (n, m), device="cuda", dtype=torch.uint8)
+    attrs = torch.arange(n, device="cuda", dtype=torch.int32)[None].contiguous()
+    idx = B.Index(codes, torch.zeros(m, 256, 1, device="cuda"), attrs, max_batch=nq, max_k=k)
+    preds = [[(0, 0, 900)]] * 8
+    lut = torch.rand(8, m, 256, device="cuda")
+    out = []
+    for mode, screened in ((0, 0), (2, 8), (0, 0)):
+        before = torch.cuda.mem_get_info()[0]
+        idx.set_option(B.OPT_SCREEN, mode)
+        taken = before - torch.cuda.mem_get_info()[0]
+        assert (taken > 30 << 20) == (mode == 2), taken                # 16 MB of lists, 16 MiB of tables
+        idx.set_option(B.OPT_GATHER, 2)
+        ids, dist = idx.search(preds, lut, k)
+        torch.cuda.synchronize()
+        assert int((idx.last_modes(8) == 2).sum()) == screened
+        out.append((ids, dist))
+    assert all(torch.equal(o[0], out[0][0]) and torch.equal(o[1], out[0][1]) for o in out)
