@@ -378,9 +378,11 @@ __global__ void invert_perm_kernel(const int32_t* __restrict__ perm, int64_t n, 
 
 }  // namespace
 
+// LDS of train_query_kernel without the staged code words: its table, the
+// candidates' values, the w_f and alpha gradients of four wavefronts.
 size_t train_query_lds_bytes(int m, int dim, int n_cand, int mr) {
-  const size_t floats = static_cast<size_t>(m) * kKsub + n_cand + 4 * static_cast<size_t>(dim) + 4 * mr;
-  return (floats + 1) / 2 * 8 + 12 * sizeof(double);
+  const size_t floats = static_cast<size_t>(m) * kKsub + n_cand + 4 * static_cast<size_t>(dim) + 4 * static_cast<size_t>(mr);
+  return floats * sizeof(float);
 }
 
 hipError_t launch_train_query(const TrainArgs& args, hipStream_t s) {

@@ -34,3 +34,26 @@ def test_train_step_shapes(B, M, dsub, nq, n_cand, n_pos, bank_rows):
     _close(_np((bank0 - bank1) / LR), ref["bank"], "bank gradient")
     _close(_np((W0 - W1) / LR), ref["W"], "W gradient")
     _close(_np(dwz), ref["w_z"], "w_z gradient")
+
+
+def test_train_step_at_the_lds_limit(B):
+    """The largest candidate list that 160 KB hold beside the table and the
+    gradients: (M 256 + n_cand + 4 D + 4 M r) floats; one more is refused."""
+    M, dsub, n_cand = 128, 1, 3584
+    say(f"[train] LDS limit M={M} n_cand={n_cand}")
+    idx, ix, q, w_z, cand, preds, n_pos = _problem(B, 11, M, dsub, (), nq=5, n_cand=n_cand, n_pos=5)
+    assert 4 * (M * 256 + n_cand + 4 * M * dsub + 4 * M * ix["r"]) == 160 * 1024
+    tau, lam = 0.8, 0.05
+    ref = _oracle(ix, q, w_z, cand, preds, n_pos, tau, lam)
+    bank0, W0 = idx.read_params()
+    loss, dwz = idx.train_step(q, preds, w_z, cand, n_pos, tau, lam, LR, want_dwz=True)
+    bank1, W1 = idx.read_params()
+    torch.cuda.synchronize()
+    _close(_np(loss), ref["loss"], "loss", rel=1e-4)
+    _close(_np((bank0 - bank1) / LR), ref["bank"], "bank gradient")
+    _close(_np((W0 - W1) / LR), ref["W"], "W gradient")
+    _close(_np(dwz), ref["w_z"], "w_z gradient")
+    more = torch.cat([cand, cand[:, :1]], 1).contiguous()
+    with pytest.raises(B.IfvsError) as e:
+        idx.train_step(q, preds, w_z, more, n_pos, tau, lam, LR)
+    assert e.value.status == B.E_UNSUPPORTED
