@@ -235,6 +235,19 @@ def scan_bytes_interval(w, sorted_attr, preds, plan, k, lut_entry):
             float((r1 - r0).sum()) * w.M)
 
 
+def scan_kind(plan):
+    """What scored a bin's batches: the list scan, the packed-table screening
+    (whose launches and fallback scan the profile counts together) or the scan."""
+    return ("list_scan_kernel" if plan.get("list_scan") else
+            "screen_kernel" if plan.get("screened") else "scan_kernel")
+
+
+def scan_ms_per_batch(scan, batches):
+    """Scan time of one batch from a profile's (ms, launches): a screened or
+    masked batch has several launches, so it is not the time per launch."""
+    return scan[0] / max(1, batches)
+
+
 def scan_union_bytes(w, sorted_attr, preds, plan, k, lut_entry, idx=None):
     """Bytes one scan launch must move between HBM and the chip at the
     least: every code tile that some query of the batch selects, read once
@@ -508,8 +521,10 @@ def main():
                     ev[s].append((b, None, None))
             eb1.record(stream)
             bin_ev[s] = (eb0, eb1)
-            plans[s] = dict(idx.last_plan(), list_scan=idx.last_coarse())
             prof_bin[s] = idx.read_profile()           # waits for this bin's kernels
+            modes = idx.last_modes(batch)
+            plans[s] = dict(idx.last_plan(), list_scan=idx.last_coarse(), screened=bool((modes == 2).any()),
+                            row_lists=bool((modes == 1).any()))
         stop.record(stream)
         torch.cuda.synchronize()
         total = start.elapsed_time(stop)
@@ -531,11 +546,11 @@ def main():
     # the timed pass brackets with events (every event record costs the
     # stream a few microseconds); the other bins' scan times come from this
     # pass.
-    _, _, stage_bin, stage_prof, stage_plans = timed_run(clus, min(args.steps, 3), profile=1,
+    _, stage_bin_runs, stage_bin, stage_prof, stage_plans = timed_run(clus, min(args.steps, 3), profile=1,
                                                          warmup=min(2, args.warmup))
     pre_time = {}
     for s in bins:
-        kk = "list_scan_kernel" if stage_plans[s].get("list_scan") else "scan_kernel"
+        kk = scan_kind(stage_plans[s])
         pre_time[kk] = pre_time.get(kk, 0.0) + stage_bin[s]["scan"][0]
     dom = max(pre_time, key=pre_time.get)
     total_ms, per_bin, prof_bin, prof, plans = timed_run(clus, args.steps,
@@ -580,22 +595,21 @@ def main():
             union_total += cache[b][2]
         ms = [m for _, m in per_bin[s]]
         sel = float(np.mean([v[1] / (w.M * w.N * batch) for v in cache.values()]))
-        # per launch: the timed pass's events where they bracket this bin's
+        # per batch: the timed pass's events where they bracket this bin's
         # scan (the dominant kernel), else the stage pass's
-        t_ms, t_n = prof_bin[s]["scan"]
-        if t_n > 0:
-            b_avg, scan_src[s] = t_ms / t_n, "timed pass"
+        if prof_bin[s]["scan"][1] > 0:
+            b_avg, scan_src[s] = scan_ms_per_batch(prof_bin[s]["scan"], len(ms)), "timed pass"
         else:
-            sm, sn = stage_bin[s]["scan"]
-            b_avg, scan_src[s] = sm / max(1, sn), "stage pass (every kernel bracketed by events)"
+            b_avg = scan_ms_per_batch(stage_bin[s]["scan"], len(stage_bin_runs[s]))
+            scan_src[s] = "stage pass (every kernel bracketed by events)"
         b_n = len(per_bin[s])
         b_ms = b_avg * b_n
         b_sec = b_avg / 1e3
         b_bytes = sum(cache[b][0] for b, _ in per_bin[s]) / max(1, b_n)
         b_gbps = b_bytes / b_sec / 1e9
         b_union = sum(cache[b][2] for b, _ in per_bin[s]) / max(1, b_n)
-        is_list = bool(plans[s].get("list_scan"))
-        kind[s] = "list_scan_kernel" if is_list else "scan_kernel"
+        kind[s] = scan_kind(plans[s])
+        is_list = kind[s] == "list_scan_kernel"
         if is_list and s in read_hist:
             # the list scan reads the first three groups' code words of each
             # tile it sums and the other words of the tiles with a row live
@@ -620,7 +634,8 @@ def main():
             fb = fabric["by_bin"][str(s)]
             roofs["hbm"]["fabric_bytes_per_launch"] = fb
             roofs["hbm"]["fabric_frac"] = round(fb / b_sec / 1e9 / HBM_PEAK_GBPS, 4)
-        if s in read_hist:
+        # (the counting build runs the tiled scan: no counts of the screening)
+        if s in read_hist and kind[s] != "screen_kernel":
             lk, lsec = lds_roof(read_hist[s], lds_rate)
             lk, lsec = lk / max(1, b_n), lsec / max(1, b_n)
             bin_lds[s] = (lk * b_n, lsec * b_n)
@@ -655,7 +670,7 @@ def main():
         k_time[kind[s]] = k_time.get(kind[s], 0.0) + bin_bytes[s][3]
     dom_bins = [s for s in bins if kind[s] == dom]
     scan_ms = sum(prof_bin[s]["scan"][0] for s in dom_bins)
-    scan_launches = sum(prof_bin[s]["scan"][1] for s in dom_bins)
+    scan_launches = sum(len(per_bin[s]) for s in dom_bins)        # batches: each scanned, or screened, once
     scan_avg_ms = scan_ms / max(1, scan_launches)
     union_per_launch = sum(bin_bytes[s][0] * bin_bytes[s][2] for s in dom_bins) / max(1, scan_launches)
     bytes_per_launch = sum(bin_bytes[s][1] * bin_bytes[s][2] for s in dom_bins) / max(1, scan_launches)
@@ -693,16 +708,19 @@ def main():
                     cache[b] = scan_bytes_bitmap(plain, w, w.preds[s][b * batch:(b + 1) * batch],
                                                  pl["qtile"], pl["splits"], k, lut_entry)[0]
                 p_bytes += cache[b]
-        p_scan_ms, p_launch = p_prof["scan"]
+        p_scan_ms = p_prof["scan"][0]
+        p_launch = args.plain_steps * len(bins)        # batches, each the tiled scan, row lists or the screening
         plain_out = {
             "qps": args.plain_steps * len(bins) * batch / (p_total / 1e3),
             "bins_qps": {str(s): batch * len(v) / (sum(m for _, m in v) / 1e3) for s, v in p_bins.items()},
             "scan_avg_ms": p_scan_ms / max(1, p_launch),
-            "scan_GBps": (p_bytes / max(1, p_launch)) / (p_scan_ms / max(1, p_launch) / 1e3) / 1e9,
+            # (the bytes are those of the tiled scan: no rate where others scored queries)
+            "scan_GBps": (None if any(p["screened"] or p["row_lists"] for p in p_plans.values()) else
+                          (p_bytes / max(1, p_launch)) / (p_scan_ms / max(1, p_launch) / 1e3) / 1e9),
             "stage_ms_per_step": {st: round(v[0] / args.plain_steps, 4) for st, v in p_prof.items()},
             "plan": p_plans[bins[-1]],
         }
-        log(f"[bench] plain layout: {plain_out['qps']:.0f} queries/s, scan {plain_out['scan_GBps']:.0f} GB/s")
+        log(f"[bench] plain layout: {plain_out['qps']:.0f} queries/s, scan {plain_out['scan_avg_ms']:.3f} ms a batch")
         # both layouts must return the same answers
         for s in bins:
             a_, f_ = clus.select_codebook(w.queries[:batch], w.preds[s][:batch],
@@ -966,7 +984,7 @@ def main():
 
     traffic = None
     if fabric is not None and all(str(s) in fabric["by_bin"] for s in dom_bins):
-        traffic = sum(fabric["by_bin"][str(s)] * prof_bin[s]["scan"][1] for s in dom_bins) / max(1, scan_launches)
+        traffic = sum(fabric["by_bin"][str(s)] * len(per_bin[s]) for s in dom_bins) / max(1, scan_launches)
     out = {
         "metric": METRIC,
         "value": qps,

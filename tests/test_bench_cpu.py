@@ -60,3 +60,12 @@ def test_lds_roof_weights_reads_by_their_rate():
     lookups, secs = bench.lds_roof(hist, rate)
     assert lookups == 64 * 10 + 8 * 4
     assert abs(secs - (10 / 1e9 + 4 / 4e9)) < 1e-18
+
+
+def test_screened_batches_are_timed_whole():
+    """A screened batch's profile counts the screening and its fallback scan:
+    the time of a batch is their sum, and the bin is not the scan kernel's."""
+    assert bench.scan_kind({"list_scan": False, "screened": True}) == "screen_kernel"
+    assert bench.scan_kind({"list_scan": True, "screened": False}) == "list_scan_kernel"
+    assert bench.scan_kind({"list_scan": False, "screened": False}) == "scan_kernel"
+    assert bench.scan_ms_per_batch((6.0, 8), 4) == 1.5
