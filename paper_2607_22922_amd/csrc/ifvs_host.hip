@@ -68,22 +68,36 @@ constexpr int kStagingSlots = 8;
 constexpr int64_t kCoarseAutoTiles = 8192;
 constexpr int kCoarseAutoM = 32;
 // Automatic screening, by W = (64-row tiles, query, subspace) triples of the
-// queries it would serve.  Measured (us, tiled scan -> screening): intervals of
-// M = 16 or 48, W = 8e6 155 -> 258, 1.9e7 339 -> 368 and 322 -> 254, 2.3e7 310
-// -> 311, 5.8e7 772 -> 466, 6.4e8 5110 -> 1640; masked, W = 4.8e7 1241 -> 445,
-// 7.7e8 8760 -> 1570 (clustered with clauses left to test row by row: 5e6 540
-// -> 197); other M, whose scan reads its tiles without looking ahead,
-// intervals of W = 4.7e5 278 -> 223, 4.7e6 688 -> 316, masked 4.8e5 287 -> 320,
-// 9.9e6 693 -> 351.  Intervals of M = 120 keep the scan: a group's packed
-// tables fill a CU's LDS and few tiles are left early (W = 1.1e8 915 -> 1189).
+// queries it would serve.  Its seven kernels take 100 to 250 us whatever W is,
+// and what it saves a triple depends on how much the queries share, so W alone
+// does not decide near the line.  Measured on mixture data, us, tiled scan ->
+// screening:
+//  * Intervals of M = 16 and 48 from W = 3e7, where none of 549 random batches
+//    loses (M = 16: 439 -> 253 at 3.4e7, 1529 -> 573 at 7.9e7; M = 48: 408 -> 301
+//    at 3.4e7, 692 -> 419 at 1e8).  Between 1e7 and 3e7 M = 16 gains (264 -> 205
+//    at 1.3e7, 453 -> 256 at 2.9e7) and M = 48 does either (at 1.9e7, half of the
+//    rows 503 -> 243, 1% of them 303 -> 402).
+//  * Intervals of M = 120 keep the scan: over 29 random batches of W >= 3e7 the
+//    screening took from 0.44 to 2.0 times its time, with no line between them
+//    (50K rows for each of k = 10 1698 -> 1163, 63K of k = 19 975 -> 1107, 4.6K of
+//    k = 100 1151 -> 2295): a group's packed tables fill a CU's LDS, and a
+//    survivor costs 120 lookups.
+//  * Intervals of other M from kScreenAutoWorkAnyM where the estimates below say
+//    so.  Five subspaces or fewer keep the scan: rows tie, and survivors fill
+//    the lists (M = 4, W = 1.2e6 233 -> 937).
+//  * Masked batches and clauses left to test row by row from 5e6 (masked 1241 ->
+//    445 at 4.8e7, 8760 -> 1570 at 7.7e8; row by row 540 -> 197 at 5e6; 2 of 631
+//    random masked batches lose, at most 1.3x), other M masked from 2e6 (287 ->
+//    320 at 4.8e5, 693 -> 351 at 9.9e6; 17 of 623 lose, at most 1.35x, all with
+//    fewer than 600 selected rows for each of the k).
 constexpr int64_t kScreenAutoWork = 30'000'000;
 constexpr int64_t kScreenAutoWorkMasked = 5'000'000;
 constexpr int64_t kScreenAutoWorkAnyM = 400'000;
 constexpr int64_t kScreenAutoWorkAnyMasked = 2'000'000;
 // The sample (every 16th block of tiles) has to hold rows about as near as the
 // k-th nearest: with fewer selected rows than this for each of the k, the
-// bound stays loose and too many rows survive (M = 120, k = 100: 100K rows
-// 700 -> 1150 us; M = 48, k = 100: 400K rows 998 -> 613).
+// bound stays loose and too many rows survive (M = 120, k = 100: 1000 rows for
+// each 797 -> 1280 us; M = 48, k = 77: 2444 for each 488 -> 329).
 constexpr int64_t kScreenRowsPerK = 2048;
 // Pools up to this share of a masked index stay with the gather scan, whose
 // time grows with the pool (4M x 48-byte codes, 256 queries: 2% 1294 us
@@ -92,6 +106,20 @@ constexpr int64_t kScreenRowsPerK = 2048;
 // a pooled row or the tiled scan's 11 ps a triple (M = 120, 6 queries of 200K
 // rows: gather 389 us, screening 490).
 constexpr int kScreenGatherPct = 3;
+// Intervals of an M without a scan of its own: us of a batch by the tiled scan
+// (whose chunks' lists the merge reads, and whose first tiles all enter the
+// pools) and by the screening, fitted to 5068 random batches (M = 6 to 64, k to
+// 100, 4 to 256 queries, W = 4e5 to 1e8, both table types).  Of 2029 others the
+// smaller estimate's path is over 5% slower than the scan for 2.7%, at most
+// 1.4x; with every such batch screened that was 36%, up to 2.2x.
+double any_m_scan_us(int k, double splits, double chunk_tiles, double work) {
+  return 80.0 + 0.124 * splits * k + 1.2 * k * std::log1p(chunk_tiles / 64.0) + 0.21 * chunk_tiles + 2.1e-5 * work;
+}
+double any_m_screen_us(int m, int k, double query_tiles, double all_tiles) {
+  return 116.0 + 1.72 * m + 3.8e-5 * all_tiles * std::sqrt(static_cast<double>(k)) +
+         0.28 * k * std::log1p(query_tiles / 64.0);
+}
+constexpr int kScreenLeastAnyM = 6;
 constexpr int kAttrSample = 4096;          // sampled values per column (pool size estimates)
 constexpr int kScreenSample = 16;          // the bound's pass: every 16th block of tiles
 constexpr int kScreenSeedTiles = 128;      // sampled 64-row tiles per query
@@ -1486,7 +1514,8 @@ void plan_screen(const ifvs_index* idx, int32_t nq, int32_t k, const DevPred* ho
                                 : (masked ? kScreenAutoWorkAnyMasked : kScreenAutoWorkAnyM);
   const bool automatic = idx->opt_screen == 0;
   const int64_t widest = shape.interval_batch ? shape.span : idx->n_tiles;
-  if (automatic && (static_cast<int64_t>(nq) * widest * idx->m < least || (shape.interval_batch && idx->m == 120)))
+  if (automatic && (static_cast<int64_t>(nq) * widest * idx->m < least ||
+                    (shape.interval_batch && (idx->m == 120 || idx->m < kScreenLeastAnyM))))
     return;
   int64_t sum_iv = 0, sum_hull = 0, max_hull = 1, served = 0;
   const bool gather_able = automatic && masked && idx->codes_rm && idx->opt_gather != 2;
@@ -1524,6 +1553,14 @@ void plan_screen(const ifvs_index* idx, int32_t nq, int32_t k, const DevPred* ho
     if (served == 0 || total_iv * idx->m < least || sum_hull * (fixed_m ? 2 : 1) > sum_iv ||
         (fixed_m && sum_iv * kTileRows < kScreenRowsPerK * k * served))
       return;
+    if (!fixed_m && !masked) {
+      const double all = static_cast<double>(total_iv), per_query = static_cast<double>(sum_iv) / served;
+      const double chunk = p.plan.chunk_tiles > 0 ? static_cast<double>(p.plan.chunk_tiles)
+                                                  : std::max<double>(p.plan.min_chunk, per_query / p.plan.splits);
+      if (any_m_scan_us(k, p.plan.splits, std::min(chunk, per_query), all * idx->m) <=
+          any_m_screen_us(idx->m, k, per_query, all))
+        return;
+    }
     if (gather_able && otherwise_us * groups / looked < 250.0 + 1.7e-6 * static_cast<double>(total_iv * idx->m)) return;
   }
   p.screen = true;

@@ -149,6 +149,28 @@ def test_screening_is_chosen_by_work_and_sharing(B):
     assert not (idx.last_modes(8) == 2).any()
 
 
+@pytest.mark.parametrize("m,n,nq,k,screened", [
+    (21, 800_003, 100, 60, True),        # the scan's and its merge's time grows with k
+    (40, 70_001, 72, 2, False),          # short intervals, few neighbours: 86 us, 167 screened
+    (30, 3_000_000, 40, 10, True),       # long intervals
+    (4, 1_500_000, 107, 9, False)])      # rows of four subspaces tie
+def test_any_subspace_count_is_screened_where_it_pays(B, m, n, nq, k, screened):
+    say(f"[screen] automatic, m={m} n={n} nq={nq} k={k}")
+    g = torch.Generator(device="cuda").manual_seed(m)
+    codes = torch.randint(0, 256, (n, m), generator=g, device="cuda", dtype=torch.uint8)
+    attrs = torch.randint(0, 1000, (1, n), generator=g, device="cuda", dtype=torch.int32)
+    idx = B.Index(codes, torch.zeros(m, 256, 1, device="cuda"), attrs, max_batch=nq, max_k=k, cluster_cols=(0,))
+    preds = [[(0, i * 7 % 900, i * 7 % 900 + 100)] for i in range(nq)]
+    lut = torch.rand(nq, m, 256, generator=g, device="cuda") ** 2
+    ids, dist = idx.search(preds, lut, k)
+    torch.cuda.synchronize()
+    assert int((idx.last_modes(nq) == 2).sum()) == (nq if screened else 0)
+    idx.set_option(B.OPT_SCREEN, 1)
+    ids1, dist1 = idx.search(preds, lut, k)
+    torch.cuda.synchronize()
+    assert torch.equal(ids, ids1) and torch.equal(dist.view(torch.int32), dist1.view(torch.int32))
+
+
 def test_equal_rows_cost_little_more_than_the_scan(B):
     """Queries whose every row ties overflow their survivor lists and are left
     to the scan: the screening gives them up early (it took five times the
@@ -261,7 +283,7 @@ print("SAME", torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1
 """
 
 
-@pytest.mark.parametrize("shape", [(5000, 4, 8, 5, (), True), (130_003, 4, 64, 5, (0,), False)],
+@pytest.mark.parametrize("shape", [(5000, 4, 8, 5, (), True), (400_003, 24, 64, 40, (0,), False)],
                          ids=["forced", "automatic"])
 def test_index_works_without_the_screening_workspace(shape):
     """The workspace is the last allocation, of the load where batches can be
