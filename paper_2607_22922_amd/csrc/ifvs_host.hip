@@ -992,7 +992,7 @@ FilterCols filter_columns(const ifvs_index* idx, const DevPred* host, int32_t nq
     if (i % kFilterGroup == 0) std::fill(count, count + kFilterCols, 0);
     const DevPred& p = host[i];
     const int nc = p.n_eff < 0 ? 0 : (residual_only ? p.n_res : p.n_eff);
-    fc.one_clause = fc.one_clause && nc <= 1;
+    fc.one_clause = fc.one_clause && nc == 1;
     for (int j = 0; j < nc; ++j) {
       const int32_t col = residual_only ? p.res_col[j] : p.col[j];
       const uint32_t lo = static_cast<uint32_t>(residual_only ? p.res_lo[j] : p.lo[j]) ^ 0x80000000u;

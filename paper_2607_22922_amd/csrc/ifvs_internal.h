@@ -128,7 +128,7 @@ constexpr int kFilterBounds = kFilterGroup * kMaxClauses * 2;
 constexpr int kFilterDirect = 8192;        // most entries of a value -> class table
 struct FilterCols {
   int32_t n = 0;                           // columns named; > kFilterCols: no classes
-  bool one_clause = true;                  // no predicate has more than one clause
+  bool one_clause = true;                  // every predicate has exactly one clause
   int32_t col[kFilterCols] = {};
   int32_t max_bounds[kFilterCols] = {};    // most bounds of any query group on the column
   // The value table's first value (unsigned order) and entry count (0: the

@@ -22,13 +22,19 @@
 //    stores alone (32 bytes per row) would take 47 us at 10M rows, the LDS
 //    mask reads and the VALU work about as long each, overlapped only as far
 //    as the 16 wavefronts per CU reach that 128 registers allow.
-//  * filter_kernel, the per-pair tests, stays for batches whose clauses name
-//    more than kFilterCols columns: per 64 rows and query one ballot, lane i
-//    keeping step i's word.
+//  * filter_kernel<true>, the pair tests of one column, for batches of one
+//    clause a query with few pairs: a wavefront stages 2048 values in LDS, lane
+//    L walks rows 32L + 31 .. 32L and shifts each of 16 queries' compare bits
+//    into a word of its own (three VALU operations per 64 pairs).
+//  * filter_kernel<false>, the general pair tests, for batches whose clauses
+//    name more than kFilterCols columns: per 64 rows and query one ballot, lane
+//    i keeping step i's word.  Bound by its chain of loads and ballots: 16
+//    queries take 420 us whether they have 10K rows or 200K.
 // Pool sizes: each workgroup sums its popcounts in LDS and writes one partial
 // count per query (no device-wide atomics); a small kernel adds the partials
 // and leaves their exclusive prefix sums for the row-list compaction.
 #include "ifvs_internal.h"
+#include "topk_device.h"
 
 namespace ifvs {
 
@@ -359,10 +365,16 @@ struct PassClauses {
   uint32_t width[kMaxClauses];
 };
 
+constexpr int kBlockPad = kBlockRows + kBlockRows / 32;   // staged block, one pad word per 32 rows
+
+// kOneClause (the launcher checks it): every query has one clause, all on
+// column `col`.
+template <bool kOneClause>
 __global__ __launch_bounds__(kFilterWaves * 64) void filter_kernel(
-    const int32_t* __restrict__ attrs, int64_t n, const DevPred* __restrict__ preds, int nq, int residual_only,
+    const int32_t* __restrict__ attrs, int64_t n, int col, const DevPred* __restrict__ preds, int nq, int residual_only,
     uint32_t* __restrict__ out, int64_t stride, uint32_t* __restrict__ count_parts) {
   __shared__ PassClauses sc[kFilterQueries];
+  __shared__ uint32_t s_vals[kOneClause ? kFilterWaves * kBlockPad : 1];
   __shared__ uint32_t s_cnt[kFilterWaves][kFilterQueries];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -394,7 +406,56 @@ __global__ __launch_bounds__(kFilterWaves * 64) void filter_kernel(
 #pragma unroll
   for (int qi = 0; qi < kFilterQueries; ++qi) cnt[qi] = 0;
 
-  if (active) {
+  if constexpr (kOneClause) {
+    if (active) {
+      const int32_t* __restrict__ values = attrs + static_cast<int64_t>(col) * n;
+      uint32_t lo[kFilterQueries], width[kFilterQueries];
+#pragma unroll
+      for (int qi = 0; qi < kFilterQueries; ++qi) {
+        lo[qi] = qi < qn ? sc[qi].lo[0] : 0;
+        width[qi] = qi < qn ? sc[qi].width[0] : 0;   // width 0: nothing passes
+      }
+      uint32_t* vals = s_vals + wave * kBlockPad;
+      for (int blk = 0; blk < kRowsPerWave / kBlockRows; ++blk) {
+        const int64_t bb = base + static_cast<int64_t>(blk) * kBlockRows;
+        // Local row r at vals[r + r / 32] (rows past n repeat the last row and
+        // are masked below).
+#pragma unroll 8
+        for (int j = 0; j < kBlockRows / 64; ++j) {
+          const int r = 64 * j + lane;
+          const int64_t i = bb + r;
+          vals[r + (r >> 5)] = static_cast<uint32_t>(values[i < n ? i : n - 1]);
+        }
+        wave_lds_fence();
+        // Lane L: rows 32L + 31 down to 32L, so row 32L + r lands in bit r.
+        uint32_t word[kFilterQueries];
+#pragma unroll
+        for (int qi = 0; qi < kFilterQueries; ++qi) word[qi] = 0;
+        const uint32_t* mine = vals + 33 * lane;
+#pragma unroll 4
+        for (int r = 31; r >= 0; --r) {
+          const uint32_t v = mine[r];
+#pragma unroll
+          for (int qi = 0; qi < kFilterQueries; ++qi)
+            word[qi] = word[qi] + word[qi] + (v - lo[qi] < width[qi] ? 1u : 0u);
+        }
+        const int64_t row0 = bb + 32 * lane;
+        uint32_t valid = ~0u;
+        if (row0 + 32 > n) valid = row0 >= n ? 0u : ((1u << static_cast<int>(n - row0)) - 1u);
+        const int64_t w32 = bb / 32 + lane;
+#pragma unroll
+        for (int qi = 0; qi < kFilterQueries; ++qi) {
+          if (qi < qn) {
+            const uint32_t wd = word[qi] & valid;
+            if (w32 < stride) out[static_cast<int64_t>(q0 + qi) * stride + w32] = wd;
+            cnt[qi] += static_cast<uint32_t>(__popc(wd));
+          }
+        }
+        // The next block overwrites vals only after every lane has read it.
+        wave_lds_fence();
+      }
+    }
+  } else if (active) {
     // held_{lo,hi}[qi] of lane L: the ballot word of step L for query qi.
     uint32_t held_lo[kFilterQueries], held_hi[kFilterQueries];
 #pragma unroll
@@ -550,19 +611,24 @@ hipError_t launch_filter_class(const int32_t* attrs, int64_t n, const FilterCols
 
 // The classes serve any batch whose clauses name 1 to kFilterCols columns:
 // their plan costs one small launch (6 us for 16 queries, 18 us for 256) whatever
-// the row count.  Measured against the per-pair tests (whole calls): 10K rows,
-// one query 25.2 us against 26.5; 100K rows, 60 queries 29.5 against 30.3; 1M
-// rows, 60 queries 30.6 against 37.5; 10M rows, 60 queries 72 against 177.
-// One clause a query, few pairs: the per-pair tests of one column are one
-// launch without a plan (390K rows, 127 queries 18.4 us against 15 + 14; 16K
-// rows, 60 queries 20.6 against 7 + 26; 1M rows, 60 queries slower, above).
+// the row count, and bounds more than kFilterDirect values apart cost them a
+// search.  Batches of exactly one clause a query on one column have the pair
+// tests of a staged column, without a plan: the faster ones while the pairs are
+// few, or no more than 2 us slower.  Whole calls, pair tests and classes: 45K
+// rows, 8 queries 40 and 38 us (bounds 9000 apart 40 and 47), 32 queries 41 and 42
+// (41 and 53), 128 queries 48 and 57 (48 and 72), 256 queries 49 and 58; 400K rows
+// the same, 256 queries 59 and 59; 1M rows, 60 queries 43.7 and 44.6, 256 queries
+// 76 and 66; 4M rows, 16 queries 45 and 42; 10M rows, 1 query 62 and 56, 256
+// queries 392 and 177.  (Two clauses: classes 43 to 63 us at 10K rows, the
+// general pair tests 209 to 374.)
 // (One group's clauses have at most kFilterBounds bounds in all, which fit
 // the LDS; groups that put that many on different columns may not.)
 bool filter_has_classes(const FilterCols& fc) {
   return fc.n >= 1 && fc.n <= kFilterCols && filter_class_lds(fc) + kFilterGroup * sizeof(uint32_t) <= kLdsBudget;
 }
 
-constexpr int64_t kPairTests = 50'000'000;   // (row, query) pairs
+constexpr int64_t kPairTests = 60'000'000;   // most (row, query) pairs and
+constexpr int64_t kPairRows = 4'000'000;     // rows for the pair tests of one column
 
 hipError_t launch_filter(const int32_t* attrs, int64_t n, const DevPred* preds, int nq, bool residual_only,
                          const FilterCols& fc, FilterPlan* plans, uint32_t* out, int64_t stride,
@@ -570,7 +636,7 @@ hipError_t launch_filter(const int32_t* attrs, int64_t n, const DevPred* preds, 
   const unsigned parts = static_cast<unsigned>(filter_count_parts(n));
   uint32_t* cp = counts ? count_parts : nullptr;
   hipError_t e = hipSuccess;
-  const bool few = fc.n == 1 && fc.one_clause && n * nq <= kPairTests;
+  const bool few = fc.n == 1 && fc.one_clause && n <= kPairRows && n * nq <= kPairTests;
   if (!few && filter_has_classes(fc)) {
     const unsigned groups = static_cast<unsigned>((nq + kFilterGroup - 1) / kFilterGroup);
     filter_plan_kernel<<<dim3(static_cast<unsigned>(fc.n), groups), dim3(kPlanThreads), 0, s>>>(
@@ -584,8 +650,9 @@ hipError_t launch_filter(const int32_t* attrs, int64_t n, const DevPred* preds, 
     }
   } else {
     const unsigned gy = static_cast<unsigned>((nq + kFilterQueries - 1) / kFilterQueries);
-    filter_kernel<<<dim3(parts, gy), dim3(kFilterWaves * 64), 0, s>>>(attrs, n, preds, nq, residual_only ? 1 : 0, out,
-                                                                    stride, cp);
+    auto* fn = few ? &filter_kernel<true> : &filter_kernel<false>;
+    fn<<<dim3(parts, gy), dim3(kFilterWaves * 64), 0, s>>>(attrs, n, fc.col[0], preds, nq, residual_only ? 1 : 0, out,
+                                                           stride, cp);
     e = hipGetLastError();
   }
   if (e != hipSuccess || !counts) return e;

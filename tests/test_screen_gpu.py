@@ -151,7 +151,7 @@ def test_screening_is_chosen_by_work_and_sharing(B):
 
 @pytest.mark.parametrize("m,n,nq,k,screened", [
     (21, 800_003, 100, 60, True),        # the scan's and its merge's time grows with k
-    (40, 70_001, 72, 2, False),          # short intervals, few neighbours: 86 us, 167 screened
+    (40, 120_001, 72, 2, False),         # short intervals, few neighbours
     (30, 3_000_000, 40, 10, True),       # long intervals
     (4, 1_500_000, 107, 9, False)])      # rows of four subspaces tie
 def test_any_subspace_count_is_screened_where_it_pays(B, m, n, nq, k, screened):
@@ -317,7 +317,7 @@ def test_small_index_takes_no_screening_workspace(B):
         before = torch.cuda.mem_get_info()[0]
         idx.set_option(B.OPT_SCREEN, mode)
         taken = before - torch.cuda.mem_get_info()[0]
-        assert (taken > 30 << 20) == (mode == 2), taken                # 16 MB of lists, 16 MiB of tables
+        assert (taken > 20 << 20) == (mode == 2), taken                # 16 MB of lists, 16 MiB of tables
         idx.set_option(B.OPT_GATHER, 2)
         ids, dist = idx.search(preds, lut, k)
         torch.cuda.synchronize()
