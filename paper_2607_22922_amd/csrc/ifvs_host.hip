@@ -85,13 +85,16 @@ constexpr int kCoarseAutoM = 32;
 //  * Intervals of other M from kScreenAutoWorkAnyM where the estimates below say
 //    so.  Five subspaces or fewer keep the scan: rows tie, and survivors fill
 //    the lists (M = 4, W = 1.2e6 233 -> 937).
-//  * Masked batches and clauses left to test row by row from 5e6 (masked 1241 ->
-//    445 at 4.8e7, 8760 -> 1570 at 7.7e8; row by row 540 -> 197 at 5e6; 2 of 631
-//    random masked batches lose, at most 1.3x), other M masked from 2e6 (287 ->
+//  * Intervals with clauses left to test row by row, of M = 16 from 5e6 (540 ->
+//    197 at 5e6) and of M = 48 from 1e7: of 511 random batches from 4e6 on, 24 of
+//    M = 48 below 1e7 lose (179 -> 218 at 5.1e6, k = 1), none above it.
+//  * Masked batches from 5e6 (1241 -> 445 at 4.8e7, 8760 -> 1570 at 7.7e8; 2 of
+//    631 random ones lose, at most 1.3x), other M masked from 2e6 (287 ->
 //    320 at 4.8e5, 693 -> 351 at 9.9e6; 17 of 623 lose, at most 1.35x, all with
 //    fewer than 600 selected rows for each of the k).
 constexpr int64_t kScreenAutoWork = 30'000'000;
 constexpr int64_t kScreenAutoWorkMasked = 5'000'000;
+constexpr int64_t kScreenAutoWorkRows48 = 10'000'000;
 constexpr int64_t kScreenAutoWorkAnyM = 400'000;
 constexpr int64_t kScreenAutoWorkAnyMasked = 2'000'000;
 // The sample (every 16th block of tiles) has to hold rows about as near as the
@@ -1510,8 +1513,11 @@ void plan_screen(const ifvs_index* idx, int32_t nq, int32_t k, const DevPred* ho
   if (idx->opt_screen == 1 || !idx->scr_tab || nq > idx->scr_batch || !screen_supported(idx->m, k)) return;
   const bool fixed_m = idx->m == 16 || idx->m == 48 || idx->m == 120;
   const bool masked = !shape.interval_batch;
-  const int64_t least = fixed_m ? (masked || shape.need_bitmap ? kScreenAutoWorkMasked : kScreenAutoWork)
-                                : (masked ? kScreenAutoWorkAnyMasked : kScreenAutoWorkAnyM);
+  const int64_t least = !fixed_m                             ? (masked ? kScreenAutoWorkAnyMasked : kScreenAutoWorkAnyM)
+                        : masked                             ? kScreenAutoWorkMasked
+                        : !shape.need_bitmap                 ? kScreenAutoWork
+                        : idx->m == 16                       ? kScreenAutoWorkMasked
+                                                             : kScreenAutoWorkRows48;
   const bool automatic = idx->opt_screen == 0;
   const int64_t widest = shape.interval_batch ? shape.span : idx->n_tiles;
   if (automatic && (static_cast<int64_t>(nq) * widest * idx->m < least ||

@@ -171,6 +171,27 @@ def test_any_subspace_count_is_screened_where_it_pays(B, m, n, nq, k, screened):
     assert torch.equal(ids, ids1) and torch.equal(dist.view(torch.int32), dist1.view(torch.int32))
 
 
+@pytest.mark.parametrize("m,n,screened", [(48, 300_007, False), (48, 900_007, True), (16, 900_007, True)])
+def test_row_by_row_clauses_are_screened_where_it_pays(B, m, n, screened):
+    """Intervals of 67 queries over 42% of the rows, a second clause tested row
+    by row: 6.4e6 triples keep the scan for M = 48, 2e7 (M = 16: 6.4e6) do not."""
+    nq, k = 67, 2
+    say(f"[screen] automatic, row by row, m={m} n={n}")
+    g = torch.Generator(device="cuda").manual_seed(m)
+    codes = torch.randint(0, 256, (n, m), generator=g, device="cuda", dtype=torch.uint8)
+    attrs = torch.randint(0, 1000, (2, n), generator=g, device="cuda", dtype=torch.int32)
+    idx = B.Index(codes, torch.zeros(m, 256, 1, device="cuda"), attrs, max_batch=nq, max_k=k, cluster_cols=(0,))
+    preds = [[(0, i * 7 % 500, i * 7 % 500 + 422), (1, 10, 990)] for i in range(nq)]
+    lut = torch.rand(nq, m, 256, generator=g, device="cuda") ** 2
+    ids, dist = idx.search(preds, lut, k)
+    torch.cuda.synchronize()
+    assert int((idx.last_modes(nq) == 2).sum()) == (nq if screened else 0)
+    idx.set_option(B.OPT_SCREEN, 1)
+    ids1, dist1 = idx.search(preds, lut, k)
+    torch.cuda.synchronize()
+    assert torch.equal(ids, ids1) and torch.equal(dist.view(torch.int32), dist1.view(torch.int32))
+
+
 def test_equal_rows_cost_little_more_than_the_scan(B):
     """Queries whose every row ties overflow their survivor lists and are left
     to the scan: the screening gives them up early (it took five times the
