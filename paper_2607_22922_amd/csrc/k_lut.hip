@@ -14,7 +14,7 @@
 // are loaded once, all in flight together, into LDS and read back as
 // broadcasts.  The 256 entries of one (query, m) row are one coalesced 1 KB
 // (fp32) or 512 B (binary16) store.  The contraction over r is
-// 8 deep and d is 2..8, far too shallow for matrix cores; the kernel is
+// 8 deep and d is at most 16, far too shallow for matrix cores; the kernel is
 // store-bound in the identity mode and a few microseconds per batch otherwise.
 //
 // With a parts array the fixed-shape kernel also writes the coarse bound's
@@ -194,10 +194,11 @@ void launch_typed(const float* q, int dim, int M, int dsub, int r, const float* 
   const dim3 g(M, (nq + kQueriesPerBlock - 1) / kQueriesPerBlock);
   const bool has_alpha = alpha != nullptr;
   bool launched = false;
-  // Every sub-dimension count whose slice of W fits the registers beside the
-  // sums (M = 21, d = 5, 37 queries in binary16: the generic kernel's loads in
-  // the innermost loop took 88 us
-  // of a call's 219, which now takes 142).
+  // Sub-dimension counts up to 16 have the fixed build (with r = 8, or without
+  // alpha): the slice of W then takes 8 d <= 128 registers.  The generic kernel
+  // loads W in its innermost loop: a call of 256 queries, M = 48, d = 10 373 us
+  // against 38 fixed, d = 16 874 and 57 (16 queries 333 and 34); d = 17 977 us,
+  // without alpha 125.
   switch (dsub) {
     case 1: launched = launch_fixed_r<1>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
     case 2: launched = launch_fixed_r<2>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
@@ -208,6 +209,13 @@ void launch_typed(const float* q, int dim, int M, int dsub, int r, const float* 
     case 7: launched = launch_fixed_r<7>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
     case 8: launched = launch_fixed_r<8>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
     case 9: launched = launch_fixed_r<9>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
+    case 10: launched = launch_fixed_r<10>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
+    case 11: launched = launch_fixed_r<11>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
+    case 12: launched = launch_fixed_r<12>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
+    case 13: launched = launch_fixed_r<13>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
+    case 14: launched = launch_fixed_r<14>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
+    case 15: launched = launch_fixed_r<15>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
+    case 16: launched = launch_fixed_r<16>(r, has_alpha, g, s, q, dim, M, cpq, W, alpha, wf, nq, out, parts, done); break;
     default: break;
   }
   if (!launched)

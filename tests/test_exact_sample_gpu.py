@@ -1,7 +1,7 @@
 """The exact search's sampled first pass: the screened plan gives the direct
 plan's ids and distance bits where pass 1 reads every tile (k of 600), every
 second or every eighth one of a wavefront (k, rows and queries decide), for row
-lengths with the fixed builds (96, 128) and without (50), intervals and masks."""
+lengths with every build, intervals and masks."""
 import pytest
 import torch
 
