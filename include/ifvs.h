@@ -218,7 +218,8 @@ ifvs_status ifvs_filtered_search(ifvs_index* idx, int32_t nq, const ifvs_predica
  * loops, harnesses that forbid allocation calls.  Same arguments and the same
  * results, bit for bit; the call allocates nothing.  Its workspace is a
  * static array of 64 MiB of device memory, one copy per GPU, placed with the
- * library's code object and held until the process ends.
+ * library's code object and held until the process ends (and the index's
+ * tables of clause bounds, sized at load).
  *  - Every call on one GPU uses that GPU's array: calls that overlap on one
  *    GPU (other streams or threads, any index handle) race and corrupt each
  *    other's results, so serialize them.  The array keeps the last call's
@@ -393,8 +394,8 @@ ifvs_status ifvs_load_vectors(ifvs_index* idx, const float* x, int32_t mem_kind)
  *   bank[row] -= lr * dL/dalpha_i for each of query i's h hashed rows,
  *   W -= lr * dL/dW.
  * C_PQ and the codes are not changed.  The arithmetic is fp32 with fp64
- * softmax statistics; the bank update uses atomics, so the order of its
- * additions (and the last bits of the result) may vary between runs.
+ * softmax statistics, every sum in a fixed order: two identical steps give
+ * identical bits.
  *
  * q: device [nq][dim]; preds: host [nq]; w_z: device [nq][dim] or NULL
  * (w_f = 1); cand: device [nq][n_cand] int32; loss_out: device [nq], L_i;
@@ -518,7 +519,8 @@ ifvs_status ifvs_encode_predicates(ifvs_index* idx, int32_t nq, const ifvs_predi
  * the codes (0 = automatic); IFVS_OPT_SPLITS forces the number of code chunks
  * a query tile is cut into (0 = automatic).  IFVS_OPT_GRID_TILES forces the
  * chunk grid of clustered-index scans (0 = automatic: a grid of about 5120
- * tiles when the widest interval spans 8192 or more 64-row tiles, else none):
+ * tiles when the widest interval spans 8192 or more 64-row tiles and the
+ * batch has enough queries to fill the GPU with its cells, else none):
  * chunk c of a query tile is then absolute grid cell c (every XCD walks the
  * same cells), or with IFVS_OPT_GRID_RELATIVE grid cell (first cell of its
  * span) + c; a span needing more cells than there are chunks is cut into
@@ -618,8 +620,9 @@ ifvs_status ifvs_read_scan_reads(ifvs_index* idx, int64_t* hist_out, void* strea
  * Errors: IFVS_E_INVALID (active_lanes out of range, NULL output), IFVS_E_HIP. */
 ifvs_status ifvs_probe_lds_gather(int32_t active_lanes, double* wave_reads_per_s, void* stream);
 
-/* ifvs_last_plan -- the launch plan of the most recent ifvs_filtered_search
- * on this index (all zero before the first): out5[0] queries per tile
+/* ifvs_last_plan -- the launch plan of the tiled scan (of the list scan, when
+ * it ran) of the most recent ifvs_filtered_search on this index, also where
+ * the screening left the scan nothing to do (all zero before the first): out5[0] queries per tile
  * (tables sharing one LDS residency and one pass over the codes), out5[1]
  * code chunks per query tile, out5[2] fewest 64-row code tiles per chunk,
  * out5[3] LDS bytes per workgroup, out5[4] chunk grid cell in tiles (0: no

@@ -22,9 +22,9 @@
 //  4. screen_rerank_kernel the listed rows' distances exactly as the scan
 //     sums them (fp32, m order), and the query's k best.
 // Measured, 256 queries: 100M x 16-byte codes, 10% selected: 1310 us for the
-// whole pass (LDS 75% busy, 10 reads a tile of 16), 300 us for the sample and
+// whole pass (LDS 80% busy, 10 reads a tile of 16), 300 us for the sample and
 // the small kernels, against the scan's 5110; 4M x 48-byte codes, half of the
-// rows masked: 1210 us (LDS 94% busy: 24 of 48 reads a tile at 6.3 CU-cycles
+// rows masked: 1200 us (LDS 94% busy: 24 of 48 reads a tile at 6.3 CU-cycles
 // each, 32 random reads on 32 banks) and 340, against 8570.
 // Exactness: every entry is >= 0 (checked; other queries keep the scan), the
 // quantization rounds down, T carries the fp32 rounding of M additions, and a
