@@ -97,6 +97,15 @@ constexpr int64_t kScreenAutoWorkMasked = 5'000'000;
 constexpr int64_t kScreenAutoWorkRows48 = 10'000'000;
 constexpr int64_t kScreenAutoWorkAnyM = 400'000;
 constexpr int64_t kScreenAutoWorkAnyMasked = 2'000'000;
+// Up to 256 queries the seed and the rerank have a CU for each; every query
+// beyond costs the screening 0.3 to 0.6 us more, which it has to save in its
+// own tiles.  Intervals of M = 48: 2497 queries of 5.8e4 triples each 1424 ->
+// 1589 us, 1862 of 7.4e4 1540 -> 1619; masked, M = 48, 1762 queries of 11% of 150K
+// rows 977 -> 1337.  With these lines 50 of 1288 random batches of 4 to 4096
+// queries are over 5% slower screened, at most 1.45x.
+constexpr int kScreenWave = 256;
+constexpr int64_t kScreenQueryWork = 100'000;         // triples of each further query
+constexpr int64_t kScreenQueryWorkAnyMasked = 30'000;
 // The sample (every 16th block of tiles) has to hold rows about as near as the
 // k-th nearest: with fewer selected rows than this for each of the k, the
 // bound stays loose and too many rows survive (M = 120, k = 100: 1000 rows for
@@ -105,10 +114,14 @@ constexpr int64_t kScreenRowsPerK = 2048;
 // Pools up to this share of a masked index stay with the gather scan, whose
 // time grows with the pool (4M x 48-byte codes, 256 queries: 2% 1294 us
 // against the screening's 2465, 5% 3336 against 2356; 10M, 3%: 4609 and 4820).
-// A masked batch is screened where that is less than the gather scan's 53 ps
-// a pooled row or the tiled scan's 11 ps a triple (M = 120, 6 queries of 200K
-// rows: gather 389 us, screening 490).
+// A masked batch is screened where that is less than the gather scan's time a
+// pooled row (gather_row_us) or the tiled scan's 11 ps a triple (M = 120, 6
+// queries of 200K rows: gather 389 us, screening 490).
 constexpr int kScreenGatherPct = 3;
+// us of the gather scan per pooled row, by the MB of the row-major codes: they
+// stay near the caches while they are small (M = 48: 210K rows 23 ps, 350K 25,
+// 980K 39, 4M and more 53).
+double gather_row_us(double mb) { return std::min(53.0, 20.0 + 0.45 * mb) * 1e-6; }
 // Intervals of an M without a scan of its own: us of a batch by the tiled scan
 // (whose chunks' lists the merge reads, and whose first tiles all enter the
 // pools) and by the screening, fitted to 5068 random batches (M = 6 to 64, k to
@@ -118,9 +131,9 @@ constexpr int kScreenGatherPct = 3;
 double any_m_scan_us(int k, double splits, double chunk_tiles, double work) {
   return 80.0 + 0.124 * splits * k + 1.2 * k * std::log1p(chunk_tiles / 64.0) + 0.21 * chunk_tiles + 2.1e-5 * work;
 }
-double any_m_screen_us(int m, int k, double query_tiles, double all_tiles) {
+double any_m_screen_us(int m, int nq, int k, double query_tiles, double all_tiles) {
   return 116.0 + 1.72 * m + 3.8e-5 * all_tiles * std::sqrt(static_cast<double>(k)) +
-         0.28 * k * std::log1p(query_tiles / 64.0);
+         0.28 * k * std::log1p(query_tiles / 64.0) + (0.12 + 0.003 * m) * std::max(0, nq - kScreenWave);
 }
 constexpr int kScreenLeastAnyM = 6;
 constexpr int kAttrSample = 4096;          // sampled values per column (pool size estimates)
@@ -1518,14 +1531,19 @@ void plan_screen(const ifvs_index* idx, int32_t nq, int32_t k, const DevPred* ho
                         : !shape.need_bitmap                 ? kScreenAutoWork
                         : idx->m == 16                       ? kScreenAutoWorkMasked
                                                              : kScreenAutoWorkRows48;
+  const int64_t further = std::max(0, nq - kScreenWave);
+  const int64_t more = fixed_m && !masked  ? further * kScreenQueryWork
+                       : !fixed_m && masked ? further * kScreenQueryWorkAnyMasked
+                                            : 0;   // (the estimates below count them)
   const bool automatic = idx->opt_screen == 0;
   const int64_t widest = shape.interval_batch ? shape.span : idx->n_tiles;
-  if (automatic && (static_cast<int64_t>(nq) * widest * idx->m < least ||
+  if (automatic && (static_cast<int64_t>(nq) * widest * idx->m < least + more ||
                     (shape.interval_batch && (idx->m == 120 || idx->m < kScreenLeastAnyM))))
     return;
   int64_t sum_iv = 0, sum_hull = 0, max_hull = 1, served = 0;
   const bool gather_able = automatic && masked && idx->codes_rm && idx->opt_gather != 2;
   if (gather_able && static_cast<int>(idx->attr_sample.size()) < idx->n_attr) return;
+  const double row_us = gather_row_us(static_cast<double>(idx->n) * idx->rw * 4e-6);
   double otherwise_us = 0.0;   // masked: what the served queries would take in the gather or the tiled scan
   // At most 16 groups are looked at, evenly spaced (the sums scaled up): the
   // planning of a batch stays within a few microseconds.
@@ -1541,7 +1559,7 @@ void plan_screen(const ifvs_index* idx, int32_t nq, int32_t k, const DevPred* ho
       if (gather_able) {
         const double share = estimate_share(idx, d);
         if (share * 100.0 <= kScreenGatherPct) continue;
-        otherwise_us += share * 100.0 <= idx->opt_gather_auto_pct ? 53e-6 * share * static_cast<double>(idx->n)
+        otherwise_us += share * 100.0 <= idx->opt_gather_auto_pct ? row_us * share * static_cast<double>(idx->n)
                                                                   : 11e-6 * static_cast<double>(b - a) * idx->m;
       }
       ++served;
@@ -1556,7 +1574,7 @@ void plan_screen(const ifvs_index* idx, int32_t nq, int32_t k, const DevPred* ho
   }
   const int64_t total_iv = sum_iv * groups / looked, total_hull = sum_hull * groups / looked;
   if (automatic) {
-    if (served == 0 || total_iv * idx->m < least || sum_hull * (fixed_m ? 2 : 1) > sum_iv ||
+    if (served == 0 || total_iv * idx->m < least + more || sum_hull * (fixed_m ? 2 : 1) > sum_iv ||
         (fixed_m && sum_iv * kTileRows < kScreenRowsPerK * k * served))
       return;
     if (!fixed_m && !masked) {
@@ -1564,10 +1582,12 @@ void plan_screen(const ifvs_index* idx, int32_t nq, int32_t k, const DevPred* ho
       const double chunk = p.plan.chunk_tiles > 0 ? static_cast<double>(p.plan.chunk_tiles)
                                                   : std::max<double>(p.plan.min_chunk, per_query / p.plan.splits);
       if (any_m_scan_us(k, p.plan.splits, std::min(chunk, per_query), all * idx->m) <=
-          any_m_screen_us(idx->m, k, per_query, all))
+          any_m_screen_us(idx->m, nq, k, per_query, all))
         return;
     }
-    if (gather_able && otherwise_us * groups / looked < 250.0 + 1.7e-6 * static_cast<double>(total_iv * idx->m)) return;
+    if (gather_able && otherwise_us * groups / looked <
+                           96.0 + 0.6 * std::max(nq, kScreenWave) + 1.7e-6 * static_cast<double>(total_iv * idx->m))
+      return;
   }
   p.screen = true;
   // About 4096 workgroups, of 64 to 4096 tiles.

@@ -192,6 +192,28 @@ def test_row_by_row_clauses_are_screened_where_it_pays(B, m, n, screened):
     assert torch.equal(ids, ids1) and torch.equal(dist.view(torch.int32), dist1.view(torch.int32))
 
 
+@pytest.mark.parametrize("nq,cluster,width,screened", [
+    (1200, (0,), 500, False), (250, (0,), 900, True), (1700, (), 110, False), (250, (), 400, True)])
+def test_large_batches_are_screened_where_each_query_has_work(B, nq, cluster, width, screened):
+    """Every query beyond 256 costs the screening its own seed and rerank:
+    many queries of few tiles keep the scan or the row lists."""
+    n, m, k = (100_003, 48, 5) if screened is False else (400_003, 48, 5)
+    say(f"[screen] automatic, nq={nq} cluster={cluster}")
+    g = torch.Generator(device="cuda").manual_seed(nq)
+    codes = torch.randint(0, 256, (n, m), generator=g, device="cuda", dtype=torch.uint8)
+    attrs = torch.randint(0, 1000, (1, n), generator=g, device="cuda", dtype=torch.int32)
+    idx = B.Index(codes, torch.zeros(m, 256, 1, device="cuda"), attrs, max_batch=nq, max_k=k, cluster_cols=cluster)
+    preds = [[(0, i * 7 % (1000 - width), i * 7 % (1000 - width) + width)] for i in range(nq)]
+    lut = torch.rand(nq, m, 256, generator=g, device="cuda") ** 2
+    ids, dist = idx.search(preds, lut, k)
+    torch.cuda.synchronize()
+    assert int((idx.last_modes(nq) == 2).sum()) == (nq if screened else 0)
+    idx.set_option(B.OPT_SCREEN, 1)
+    ids1, dist1 = idx.search(preds, lut, k)
+    torch.cuda.synchronize()
+    assert torch.equal(ids, ids1) and torch.equal(dist.view(torch.int32), dist1.view(torch.int32))
+
+
 def test_equal_rows_cost_little_more_than_the_scan(B):
     """Queries whose every row ties overflow their survivor lists and are left
     to the scan: the screening gives them up early (it took five times the
