@@ -65,3 +65,26 @@ def test_every_build_matches_direct(B, dim):
         torch.cuda.synchronize()
         out.append((ids, dist.view(torch.int32)))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+def test_intervals_within_the_error_bound(B):
+    """Short intervals of long rows, whose distances lie within the screening's
+    error bound of each other: nearly every row is a candidate, and the lists
+    hold each exactly once."""
+    n, dim, nq, k = 20_000, 400, 333, 4
+    say("[exact] dense candidates")
+    g = torch.Generator(device="cuda").manual_seed(7)
+    attrs = torch.randint(0, 1000, (1, n), generator=g, device="cuda", dtype=torch.int32)
+    x, q = (torch.randn(r, dim, generator=g, device="cuda") for r in (n, nq))
+    idx = B.Index(torch.zeros(n, 1, dtype=torch.uint8, device="cuda"), torch.zeros(1, 256, dim, device="cuda"), attrs,
+                  max_batch=nq, max_k=700, cluster_cols=(0,))
+    idx.load_vectors(x)
+    preds = [[(0, i % 970, i % 970 + 1 + i % 30)] for i in range(nq)]
+    for kk in (k, 700):
+        out = []
+        for plan in (2, 1):
+            idx.set_option(B.OPT_EXACT_PLAN, plan)
+            ids, dist = idx.exact_search(q, preds, kk)
+            torch.cuda.synchronize()
+            out.append((ids, dist.view(torch.int32)))
+        assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
