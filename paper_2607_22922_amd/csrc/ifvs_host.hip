@@ -317,7 +317,7 @@ struct ifvs_index {
   float* xr = nullptr;           // [n][dim] fp32, physical order
   uint4* xb = nullptr;           // [ceil(n/32)][ksteps][64] bf16 fragments
   float* xn = nullptr;           // [ceil(n/32)*32] squared norms
-  unsigned* xmax = nullptr;      // largest row norm (fp32 bits)
+  unsigned* xmax = nullptr;      // [2] largest row norm, largest movement by the rounding to bf16 (fp32 bits)
   unsigned long long* xbad = nullptr;
   uint4* qb = nullptr;           // query fragments
   float* qn_x = nullptr;         // [max_batch] |q|^2
@@ -2099,7 +2099,7 @@ ifvs_status attach_vectors(ifvs_index* idx, const float* src, const int32_t* src
   if ((st = dev_alloc(&idx->xb, static_cast<size_t>(n32 / 32) * ks * 64, "bf16 vector fragments")) != IFVS_OK)
     return bail(st);
   if ((st = dev_alloc(&idx->xn, static_cast<size_t>(n32), "vector norms")) != IFVS_OK) return bail(st);
-  if ((st = dev_alloc(&idx->xmax, 1, "largest norm")) != IFVS_OK) return bail(st);
+  if ((st = dev_alloc(&idx->xmax, 2, "largest norm")) != IFVS_OK) return bail(st);
   if ((st = dev_alloc(&idx->xbad, 1, "non-finite count")) != IFVS_OK) return bail(st);
   // Workspace of the searches: chunks and bins per query are bounded so the
   // buffers stay small; the planner never exceeds them.
@@ -2122,7 +2122,7 @@ ifvs_status attach_vectors(ifvs_index* idx, const float* src, const int32_t* src
   if ((st = dev_alloc(&idx->partials_x, static_cast<size_t>(max_batch) * idx->exact_chunks_max * idx->max_k,
                       "exact top-k partials")) != IFVS_OK)
     return bail(st);
-  hipError_t e = hipMemset(idx->xmax, 0, sizeof(unsigned));
+  hipError_t e = hipMemset(idx->xmax, 0, 2 * sizeof(unsigned));
   if (e == hipSuccess) e = hipMemset(idx->xbad, 0, sizeof(unsigned long long));
   if (e == hipSuccess)
     e = launch_exact_stage(src, n, dim, src_perm, idx->xt, idx->xr, idx->xb, idx->xn, idx->xmax, idx->xbad, 0);

@@ -43,16 +43,20 @@ constexpr int kExKC = 8;           // K steps (16 dims each) loaded per round
 // Row lengths of up to kExKeep K steps (128 dimensions) keep the query tile's
 // fragments and the next row tile's in registers: 8 VGPRs a step beside about
 // 60, which fills the 128 of sixteen wavefronts per CU at 8 steps (pass 2 then
-// spills five).  Longer rows load both in the loop.  4M rows, 256 queries of 10% / 50%, us
-// with the loads in the loop -> held: 16 dimensions 323 / 540 -> 314 / 417, 32:
-// 318 / 591 -> 283 / 537, 64: 352 / 639 -> 322 / 638, 112: 501 / 963 -> 459 /
-// 914, 128: 558 / 1096 -> 529 / 1073.
+// spills five).  Longer rows load both in the loop.  4M rows, 256 queries of 10% /
+// 50%, us with the loads in the loop -> held: 32 dimensions 344 / 591 -> 307 / 475,
+// 112: 501 / 963 -> 459 / 914, 128: 541 / 1044 -> 518 / 995.
 constexpr int kExKeep = 8;
 
 // fp32 -> bf16 bits, round to nearest even (finite inputs).
 __device__ __forceinline__ uint32_t bf16_bits(float f) {
   const uint32_t u = __float_as_uint(f);
   return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+}
+
+// How far that rounding moves a value (infinite where it overflows).
+__device__ __forceinline__ double bf16_error(float f) {
+  return static_cast<double>(f) - static_cast<double>(__uint_as_float(bf16_bits(f) << 16));
 }
 
 // Eight consecutive values of a row (zero past `dim`) as one MFMA fragment.
@@ -75,8 +79,8 @@ __device__ __forceinline__ uint4 pack_fragment(const float* __restrict__ row, in
 // order) and the
 // bf16 fragments of its 32-row tile (xb[(tile32 * ks + s) * 64 + lane]: lane
 // l holds row l % 32, dims s * 16 + (l / 32) * 8 .. + 8).  Also the largest
-// norm (as fp32 bits; norms are non-negative) and a count of non-finite
-// values.
+// norm and, after it, the largest movement by the rounding to bf16 (as fp32
+// bits; both are non-negative) and a count of non-finite values.
 __global__ __launch_bounds__(256) void exact_stage_kernel(const float* __restrict__ x, int64_t n, int dim,
                                                           int ks, const int32_t* __restrict__ perm,
                                                           float* __restrict__ xt, float* __restrict__ xr,
@@ -89,10 +93,13 @@ __global__ __launch_bounds__(256) void exact_stage_kernel(const float* __restric
   const bool real = r < n;
   const float* src = real ? x + static_cast<size_t>(perm ? perm[r] : r) * dim : nullptr;
   float acc = 0.0f;
+  double moved = 0.0;
   unsigned nonfinite = 0;
   if (real) {
     for (int j = 0; j < dim; ++j) {
       const float v = src[j];
+      const double by = bf16_error(v);
+      moved += by * by;
       xt[(static_cast<size_t>(r >> 6) * dim + j) * 64 + (r & 63)] = v;
       xr[static_cast<size_t>(r) * dim + j] = v;
       acc = __fadd_rn(acc, __fmul_rn(v, v));
@@ -109,15 +116,16 @@ __global__ __launch_bounds__(256) void exact_stage_kernel(const float* __restric
     }
   if (real) {
     atomicMax(max_norm_bits, __float_as_uint(sqrtf(acc)));
+    atomicMax(max_norm_bits + 1, __float_as_uint(static_cast<float>(sqrt(moved) * (1.0 + 0x1p-22))));
     if (nonfinite) atomicAdd(bad, static_cast<unsigned long long>(nonfinite));
   }
 }
 
 // ------------------------------------------------------------ query prep
 // One wavefront per query position p (original query qorder[p]): its bf16
-// fragments in 32-query tiles, |q|^2, and eps(p) (see the header), computed
-// in fp64 from the largest row norm X and |q| and rounded up.  Also clears
-// the position's candidate count.
+// fragments in 32-query tiles, |q|^2, and eps(p) (exact_eps), computed in fp64
+// from the rows' largest norm and rounding and the query's, and rounded up.
+// Also clears the position's candidate count.
 __global__ __launch_bounds__(64) void exact_query_kernel(const float* __restrict__ q, int dim, int ks, int nq,
                                                          const int32_t* __restrict__ qorder,
                                                          const unsigned* __restrict__ max_norm_bits,
@@ -134,17 +142,19 @@ __global__ __launch_bounds__(64) void exact_query_kernel(const float* __restrict
     qb[(static_cast<size_t>(t) * ks + step) * 64 + h * 32 + lane_lo] = f;
   }
   if (!real) return;
-  double s2 = 0.0;
+  double s2 = 0.0, moved = 0.0;
   float acc = 0.0f;
   if (lane == 0) {
     for (int j = 0; j < dim; ++j) {
+      const double by = bf16_error(row[j]);
       acc = __fadd_rn(acc, __fmul_rn(row[j], row[j]));
       s2 += static_cast<double>(row[j]) * row[j];
+      moved += by * by;
     }
     const double qnorm = sqrt(s2);
     const double X = static_cast<double>(__uint_as_float(*max_norm_bits));
     qn[p] = acc;
-    eps[p] = exact_eps(dim, X, qnorm);
+    eps[p] = exact_eps(dim, X, __uint_as_float(max_norm_bits[1]), qnorm, sqrt(moved));
     cand_n[p] = 0;
   }
 }

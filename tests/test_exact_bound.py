@@ -17,11 +17,12 @@ def eps(tmp_path_factory):
     d = tmp_path_factory.mktemp("exact_bound")
     src, lib = d / "b.cpp", d / "b.so"
     src.write_text('#include "exact_bound.h"\n'
-                   'extern "C" float eps(int dim, double x, double q) { return ifvs::exact_eps(dim, x, q); }\n')
+                   'extern "C" float eps(int dim, double x, double xe, double q, double qe) {\n'
+                   '  return ifvs::exact_eps(dim, x, xe, q, qe);\n}\n')
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-D__host__=", "-D__device__=", "-I", CSRC, str(src),
                     "-o", str(lib)], check=True)
     fn = ctypes.CDLL(str(lib)).eps
-    fn.argtypes, fn.restype = [ctypes.c_int, ctypes.c_double, ctypes.c_double], ctypes.c_float
+    fn.argtypes, fn.restype = [ctypes.c_int] + [ctypes.c_double] * 4, ctypes.c_float
     return fn
 
 
@@ -56,7 +57,8 @@ def test_bound_holds(eps, dim, kind):
     x, q = _rows(kind, dim, np.random.default_rng(dim))
     d = np.add.accumulate((x - q) ** 2, axis=-1, dtype=np.float32)[:, -1].astype(np.float64)
     norm = lambda a: np.sqrt((a.astype(np.float64) ** 2).sum(-1))
-    bound = eps(dim, norm(x).max(), norm(q))
+    moved = lambda a: norm(a.astype(np.float64) - _bf16(a).astype(np.float64))
+    bound = eps(dim, norm(x).max(), moved(x).max(), norm(q), moved(q))
     err = np.abs(_dd(x, q).astype(np.float64) - d).max()
     assert err <= bound
     if kind == "one way" and dim >= 16:
