@@ -43,9 +43,11 @@ constexpr int kExKC = 8;           // K steps (16 dims each) loaded per round
 // Row lengths of up to kExKeep K steps (128 dimensions) keep the query tile's
 // fragments and the next row tile's in registers: 8 VGPRs a step beside about
 // 60, which fills the 128 of sixteen wavefronts per CU at 8 steps (pass 2 then
-// spills five).  Longer rows load both in the loop.  4M rows, 256 queries of 10% /
-// 50%, us with the loads in the loop -> held: 32 dimensions 344 / 591 -> 307 / 475,
-// 112: 501 / 963 -> 459 / 914, 128: 541 / 1044 -> 518 / 995.
+// spills five).  Longer rows load both in the loop.  4M rows, 256 queries of 10% / 50%, us
+// with the loads in the loop -> held (one run, eps from 2^-8 for every value and an
+// atomic per candidate on both sides): 16 dimensions 323 / 540 -> 314 / 417, 32:
+// 318 / 591 -> 283 / 537, 64: 352 / 639 -> 322 / 638, 112: 501 / 963 -> 459 /
+// 914, 128: 558 / 1096 -> 529 / 1073.
 constexpr int kExKeep = 8;
 
 // fp32 -> bf16 bits, round to nearest even (finite inputs).
